@@ -271,11 +271,11 @@ moe_status prefill_impl(moe_layer* l, int32_t T, const void* x, float* y,
   HIP_TRY(launch_route_prefill(route_params(l, T, x), route_out(ws, idx, w, prec),
                                ws.wl, ws.perm, ws.pos, s), "route kernel launch");
   HIP_TRY(mark(l, 1, s), "timing event");
-  HIP_TRY(launch_prefill_up(l->d_table, ws.wl, ws.perm, static_cast<const f16*>(x),
-                            ws.h, T, d, f, K, mg, s), "prefill up launch");
+  HIP_TRY(launch_prefill_up(l->d_table, ws.wl, ws.perm, static_cast<const f16*>(x), ws.h, T, d,
+                            f, l->desc.n_experts, K, mg, s), "prefill up launch");
   HIP_TRY(mark(l, 2, s), "timing event");
-  HIP_TRY(launch_prefill_down(l->d_table, ws.wl, ws.h, ws.eperm, T, d, f, K, mg, s),
-          "prefill down launch");
+  HIP_TRY(launch_prefill_down(l->d_table, ws.wl, ws.h, ws.eperm, T, d, f, l->desc.n_experts, K,
+                              mg, s), "prefill down launch");
   HIP_TRY(mark(l, 3, s), "timing event");
   HIP_TRY(launch_combine_prefill(ws.eperm, ws.pos, ws.w, ws.prec, T, d, K, y,
                                  h_res, static_cast<f16*>(x_next), l->desc.rms_eps, s),

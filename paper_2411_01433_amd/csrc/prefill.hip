@@ -1,6 +1,7 @@
-// Prefill path: the experts of Eq. 1 as an MFMA grouped GEMM with the
-// quantised copies (int4 / int2 low copies, the int8 high copy of an int8
-// model) dequantised in registers, then the weighted combine.
+// Prefill path (and large decode batches): the experts of Eq. 1 as an MFMA
+// grouped GEMM with the quantised copies (int4 / int2 low copies, the int8
+// high copy of an int8 model) dequantised in registers, then the weighted
+// combine.
 //
 //   up:    H[j, r] = silu(X_g W1^T)[j, r] * (X_g W3^T)[j, r]     (fp16 out)
 //   down:  E[j, r] = (H_g W2^T)[j, r]                             (fp32 out)
@@ -13,31 +14,63 @@
 // offset + j), so the down kernel reads contiguous rows and the combine
 // finds each pair through pos[].
 //
-// Tiling (v_mfma_f32_16x16x32_f16: lane l holds A[l%16][8(l/16)+i],
-// B[8(l/16)+i][l%16] and C[4(l/16)+i][l%16]): M = tokens (A = activations
-// from LDS, up to 160 per pass = 10 tiles), N = weight rows (B = weight
-// rows, each lane's 8 k-values contiguous in memory), K = reduction dim in
-// stages of 64.  A block of 4 waves owns 64 rows of W1 and W3 (16 per wave)
-// in the up-projection and 128 rows of W2 (32 per wave) in the
-// down-projection; each wave covers its rows for all the pass's tokens (up
-// to 160), so every weight element is fetched from HBM once per pass and
-// used by every token of the group.  Activations are double-buffered in
-// LDS (one barrier per stage, later stages fetched into registers ahead of
-// use) and weight fragments go straight into a ring of registers (see
-// gemm_pass for the pipeline):
-//   fp16: lane group g (= l/16) reads 16 B at k = 32s + 8g for step s;
-//   int8: lane group g reads the 16 B of columns 16g..16g+15 of the stage
-//         and step s uses its words 2s, 2s+1;
-//   int4: lane group g reads the 8 B half group of columns 16g..16g+15 of
-//         the stage and step s uses its word s;
-//   int2: lane group g reads the 4 B of the same columns, half-word s.
-// One load instruction covers 64 of each row's 128 stage bytes, so weight
-// loads are plain (the line stays in L2 for the other half; nontemporal
-// loads measured 20% more HBM traffic here).  Low codes are turned into
-// fp16 with the 0x6400|u == 1024+u trick and scaled by the group's fp16
-// scale (w = fp16(q*s)); the pair order this produces,
-// (e0,e4)(e1,e5)(e2,e6)(e3,e7), is matched by staging the activations in
-// LDS with the same permutation inside every 8 elements.
+// What bounds it.  With hundreds of tokens per expert the products do, and
+// what feeds them: the LDS port, and the cycles in which a wave issues loads
+// instead of products.  With few tokens the HBM stream of the weights does.
+// A block is 4 waves, one per SIMD and with the whole unit's registers and
+// LDS, and owns 64 RT weight rows (in the up-projection half of them W1, the
+// other half the same rows of W3) x up to 256 tokens; a wave owns 32 RT rows
+// x half of the tokens as v_mfma_f32_32x32x16_f16 tiles (weights are the A
+// operand: lane l holds A[l%32][8(l/32)+i], B[8(l/32)+i][l%32] and
+// C[8(i/4)+4(l/32)+i%4][l%32]).  At RT = 4 and 256 tokens a step of 16
+// columns reads 8 fragments from LDS for 16 products.
+//
+// Staging.  Both operands go to LDS by direct global-to-LDS loads of 16
+// bytes per lane: activations (gathered through the permutation) in stages
+// of 64 columns, 8 rows x one full 128-byte line per load; fp16 weights the
+// same; codes as they are stored, in units of 64 bytes per row (16 rows per
+// load) = 1, 2 or 4 stages of int8, int4 or int2; group scales in units of
+// 16 bytes per row = 4 stages.  Each sits in a ring of 3 to 8 slots (see
+// Ring).  A code row whose last unit is partial reads its first chunk
+// instead, and scales past the row its last dword, which no product uses;
+// rows past the matrix or the group repeat the last one and are not stored.
+// Nothing outside a row is read.
+//
+// Bank conflicts.  The 16-byte chunk c of row r sits at position c ^ ((r/2)
+// % 8) of a 128-byte LDS row, c ^ ((r/4) % 4) of a 64-byte one (the loads
+// permute the source chunks inside the line), so that 16 consecutive rows of
+// a fragment read cover the 64 banks: the counters show none, and with the
+// swizzle made for 32 banks half of the LDS cycles were conflicts.
+//
+// Products.  The reduction order inside an MFMA is free as long as both
+// operands agree: lane (row = l % 32, half = l / 32) takes columns 32 half +
+// 8 s .. + 7 of the stage in step s = 0..3.  A lane's columns of a stage are
+// then one quantisation group: 32 int4 codes are one 16-byte read, and the
+// lane needs one scale.  Codes become fp16(q * s) in registers after the
+// read, in column order.
+//
+// Pipeline.  Fragments of step s + 1 are read (and converted) between the
+// products of step s, two quarters of a step before their use; the barrier
+// between stages stands before the last step's products, so that the next
+// stage's first fragments are read under those.  A stage's loads are spread
+// over the quarters of a stage, one or two each: a load that finds the
+// memory pipe full holds up the wave's products.  The loads are inline
+// assembly without register results (the compiler would otherwise wait for
+// all of them before every LDS read); the waits are explicit counts.
+//
+// Measured (one layer, up / down-projection, us; before: 16x16x32 products,
+// 16 or 32 weight rows per wave, 160 tokens per pass, weights in register
+// rings, activations through LDS):
+//   Mixtral shape, 4:3:1 fp16:int4:int2, 8192 tokens 5863 / 3407 -> 3529 /
+//   1905 (1.09 and 1.01 PFLOP/s; a large fp16 library GEMM reaches 1.48),
+//   512 tokens 455 / 292 -> 443 / 267; half fp16 half int4, 64 tokens 369 /
+//   184 -> 326 / 186; Phi shape, 1024 tokens 441 / 257 -> 410 / 194; d 320,
+//   f 448, 6 experts, 1024 tokens 43 / 33 -> 14 / 17.
+// On the way, at 8192 tokens and fp16 only (up): 8 waves of 64 rows x 128
+// tokens 3.85 ms; 4 waves 3.70; fragment reads two quarters early and the
+// short SwiGLU 3.60; remainders last 3.55; three activation stages instead
+// of two 3.38.
+#include <cstddef>
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -46,469 +79,612 @@ namespace moe {
 
 namespace {
 
-// 4 waves per block; two blocks per compute unit in the up-projection, so
-// that a stage barrier holds only its block's waves and the other block
-// runs meanwhile.
 constexpr int kThreads = 256;
-constexpr int kWaves = 4;
-constexpr int kStageK = 64;               // reduction columns per stage (2 MFMA steps)
-constexpr int kSteps = kStageK / 32;
-constexpr int kPassTok = 160;             // tokens per pass (10 MFMA tiles)
-constexpr int kTokTiles = kPassTok / 16;
-constexpr int kLdsRow = kStageK + 8;      // halves per staged row (16 B pad)
-constexpr int kUpRowsW = 16;              // weight rows per wave, up-projection
-// staging: thread t owns rows (t >> 3) + 32 i of the pass and 8-column piece t & 7
-constexpr int kPieces = kStageK / 8;
-constexpr int kStageRowsPerThread = kPassTok / (kThreads / kPieces);
+constexpr int kStageK = 64;                       // columns per stage, 4 steps of 16
+constexpr int kTileTok = 256;                     // tokens per block (MT = 4)
+constexpr int kScaleStages = 4;                   // stages per unit of scales
+constexpr uint32_t kLdsBytes = 160 * 1024;
+constexpr int kMaxSlots = 8;
 
-typedef __attribute__((address_space(1))) const u32x4* gvec4;
+// Geometry of a block of 64 RT weight rows (a wave: RT tiles of 32) and 64
+// MT tokens (a wave: MT tiles of 32), and its LDS rings: kASlots stages of
+// activations (128 bytes of each row), kWSlots units of weights (fp16: 128
+// bytes of each row = one stage, codes: 64 bytes = kUnit stages) and of
+// scales (16 bytes of each row).  All rings are as deep as the LDS allows;
+// the largest fp16 blocks have room for two units of weights, whose loads
+// go first in a stage and arrive within it, while the activations have two
+// stages.
+template <int BITS, int RT, int MT> struct Ring {
+  static constexpr int kRows = 64 * RT;
+  static constexpr int kSubRows = kRows / 2;       // rows of each of the two sub-blocks
+  static constexpr int kRowBytes = BITS == 16 ? 128 : 64;
+  static constexpr int kUnit = BITS == 16 ? 1 : 8 / BITS;
+  static constexpr uint32_t kASlot = MT * 64 * 128;
+  static constexpr uint32_t kWSlot = kRows * kRowBytes;
+  static constexpr uint32_t kSSlot = BITS == 16 ? 0 : kRows * 16;
+  static constexpr int kFit = (int)(kLdsBytes / (kASlot + kWSlot + kSSlot));
+  static constexpr int kASlots = kFit < 3 ? 3 : kFit < kMaxSlots ? kFit : kMaxSlots;
+  static constexpr int kWSlots = kFit < 3 ? 2 : kASlots;
+  static constexpr uint32_t kWBase = kASlots * kASlot;
+  static constexpr uint32_t kSBase = kWBase + kWSlots * kWSlot;
+  static_assert(kSBase + kWSlots * kSSlot <= kLdsBytes, "LDS");
+  // loads per wave: activations per stage, weights and scales per unit, and
+  // the fewest of those that a stage issues
+  static constexpr int kALoads = 2 * MT;
+  static constexpr int kWUnitLoads = RT * kRowBytes / 64;
+  static constexpr int kSUnitLoads = BITS == 16 ? 0 : RT;
+  static constexpr int kWLoads = kWUnitLoads / kUnit, kSLoads = kSUnitLoads / kScaleStages;
+  static constexpr int kLoads = kWLoads + kSLoads + kALoads;
+  // loads that may be in flight when a stage ends: those of the stages
+  // after the next one
+  static constexpr int kPending = kWSlots == 2 ? kALoads : (kASlots - 2) * kLoads;
+};
 
-template <class T>
-__device__ inline const __attribute__((address_space(1))) T* gmem(const T* p) {
-  return (const __attribute__((address_space(1))) T*)p;
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+
+// 16 (4) bytes per lane from base + off to LDS at lds + 16 (4) * lane.
+// lds and base are wave-uniform.  m0 holds the LDS address (the compiler
+// keeps nothing in it on this target); one wait state is required between
+// its write and the load.
+__device__ inline void lds_load16(uint32_t lds, const uint8_t* base, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds), "v"(off), "s"(base) : "memory");
+}
+__device__ inline void lds_load4(uint32_t lds, const uint8_t* base, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               :: "s"(lds), "v"(off), "s"(base) : "memory");
+}
+// All but the N newest loads of this wave are in LDS and every LDS read of
+// it has returned, then the block's barrier.
+template <int N>
+__device__ inline void stage_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 
 __device__ inline f16x2 as_h2(uint32_t v) { return __builtin_bit_cast(f16x2, v); }
 __device__ inline uint32_t as_u32(f16x2 v) { return __builtin_bit_cast(uint32_t, v); }
 
-__device__ inline f16x8 pack8(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  return __builtin_bit_cast(f16x8, u32x4{a, b, c, d});
+constexpr uint32_t kAndOr = 0xEA;  // v_bitop3 truth table of (a & b) | c
+__device__ inline uint32_t scaled(uint32_t v, uint32_t bias, f16x2 s2) {
+  return as_u32((as_h2(v) - as_h2(bias)) * s2);
 }
 
-// Position of element i of an 8-block in the staged activation layout for
-// low-precision groups: x0 x4 x1 x5 x2 x6 x3 x7.
-__device__ inline int perm8(int i) { return i < 4 ? 2 * i : 2 * (i - 4) + 1; }
+// A code u whose lowest bit sits at bit p of a 16-bit half, or-ed with the
+// exponent of 2^(10-p), is the fp16 number 2^(10-p) + u; a packed subtract
+// of 2^(10-p) + 2^(bits-1) and a packed multiply by the scale give fp16(q s).
+// frag(q, s): the 8 codes of step s of a lane's 32 (its half of a stage), in
+// column order.
+template <int BITS> struct Codes;
 
-// Activation staging of one pass.  Thread t owns rows (t >> 3) + 32 i of
-// the pass and the 8-column piece t & 7 of every stage; the source rows
-// are resolved once per pass (group row j is token perm[off + j] / K of x,
-// or row off + j of H which is already in group order), then each stage
-// is fetched into registers ahead of use and written to LDS [row][k].
-// Rows beyond n repeat row n - 1 (row j of a product depends on row j of
-// the activations only, and those rows are not stored) and stages past the
-// end reload stage 0: every load is unconditional, so that no branch hides
-// a load from the compiler's wait counting, which would then wait for all
-// loads in flight (the weight prefetch included) at every stage.
-// Rows are held as 32-bit byte offsets from a block-uniform base (the
-// gathered token rows of x lie within T * d_model halves, a group's rows of
-// H within kPassTok * d_ff), which leaves registers for a deeper ring.
-struct ActStager {
-  const char* base;
-  uint32_t row[kStageRowsPerThread];
-  u32x4 v[3][kStageRowsPerThread];  // up to three stages in flight
-
-  __device__ void init(const f16* src, int64_t ld, const int32_t* perm, int off,
-                       int j0, int n, int K, bool gather) {
-    base = reinterpret_cast<const char*>(gather ? src : src + (int64_t)(off + j0) * ld);
-#pragma unroll
-    for (int i = 0; i < kStageRowsPerThread; ++i) {
-      const int r = min((int)(threadIdx.x / kPieces) + (kThreads / kPieces) * i, n - 1);
-      const int64_t sr = gather ? perm[off + j0 + r] / K : (int64_t)r;
-      row[i] = (uint32_t)((sr * ld + (threadIdx.x % kPieces) * 8) * 2);
-    }
-  }
-  template <int SLOT>
-  __device__ void fetch(int64_t ld, int64_t k0) {
-    const char* b = base + 2 * (k0 < ld ? k0 : 0);
-#pragma unroll
-    for (int i = 0; i < kStageRowsPerThread; ++i)
-      v[SLOT][i] = *reinterpret_cast<const u32x4*>(b + row[i]);
-  }
-  template <int SLOT, bool PERMUTE>
-  __device__ void store(f16* lds) const {
-#pragma unroll
-    for (int i = 0; i < kStageRowsPerThread; ++i) {
-      u32x4 x = v[SLOT][i];
-      if (PERMUTE) {
-        const f16x8 a = __builtin_bit_cast(f16x8, x);
-        f16x8 b;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) b[perm8(e)] = a[e];
-        x = __builtin_bit_cast(u32x4, b);
-      }
-      const int r = (threadIdx.x / kPieces) + (kThreads / kPieces) * i;
-      *reinterpret_cast<u32x4*>(lds + r * kLdsRow + (threadIdx.x % kPieces) * 8) = x;
-    }
-  }
-};
-
-// int4 / int2 groups stage their activations permuted (perm8); fp16 and
-// int8 groups in column order.
-template <int BITS> constexpr bool kPermuted = BITS == 4 || BITS == 2;
-
-// A fragment (activations) of token tile tt for step s of the stage.
-template <int BITS>
-__device__ inline f16x8 a_frag(const f16* lds, int tt, int s) {
-  const int l = threadIdx.x & 63, g = l >> 4;
-  const int col = BITS == 16 ? 32 * s + 8 * g : 16 * g + 8 * s;
-  return *reinterpret_cast<const f16x8*>(lds + (tt * 16 + (l & 15)) * kLdsRow + col);
-}
-
-// Per-lane sources of one matrix M for one pass: the lane's weight row
-// (codes or fp16) and scale row, advanced to its lane group's first column
-// of a stage (fp16: 8g; codes: 16g, one scale per 32 columns).  Resolved
-// once per pass with M a compile-time index, so the expert entry is never
-// indexed at run time (that would put it in scratch memory, and a scratch
-// load makes the wait before it cover every load in flight).
-// Held as block-uniform bases and 32-bit per-lane byte offsets (a matrix
-// is at most 2^30 weights), which the loads take as base + offset.
-template <int BITS> struct WRow {
-  const uint8_t* w;   // block-uniform
-  const uint8_t* s;   // block-uniform
-  uint32_t wo, so;    // this lane's byte offsets
-};
-
-template <int BITS, int M>
-__device__ inline WRow<BITS> wrow(const ExpertEntry& ex, int64_t row, int64_t ld) {
-  const int g = (threadIdx.x & 63) >> 4;
-  WRow<BITS> r;
-  if (BITS == 16) {
-    r.w = reinterpret_cast<const uint8_t*>(ex.w[M]);
-    r.wo = (uint32_t)((row * ld + 8 * g) * 2);
-    r.s = nullptr;
-    r.so = 0;
-  } else {
-    r.w = BITS == 8 ? ex.hq[M] : ex.q[M];
-    r.s = reinterpret_cast<const uint8_t*>(BITS == 8 ? ex.hs[M] : ex.s[M]);
-    r.wo = (uint32_t)(row * (ld * BITS / 8) + 16 * g * BITS / 8);
-    r.so = (uint32_t)((row * (ld / kGroup) + (g >> 1)) * 2);
-  }
-  return r;
-}
-
-// Weight fragments of one 16-row tile of one matrix for one stage at
-// column k0 (a multiple of 64).
-template <int BITS> struct WFrag;
-
-template <> struct WFrag<16> {
-  u32x4 v[kSteps];
-  __device__ inline void load(const WRow<16>& r, int64_t k0) {
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s)
-      v[s] = *gmem(reinterpret_cast<const u32x4*>(r.w + 2 * (k0 + 32 * s) + r.wo));
-  }
-  __device__ inline f16x8 get(int s) const { return __builtin_bit_cast(f16x8, v[s]); }
-};
-
-// Scales are held zero-extended in a register of their own: packed two to
-// a register, each insertion waits for its load at once.
-__device__ inline f16x2 splat_scale(uint32_t sc) {
-  return as_h2(__builtin_amdgcn_perm(sc, sc, 0x01000100u));
-}
-__device__ inline uint32_t load_scale(const uint8_t* p) {
-  return *gmem(reinterpret_cast<const uint16_t*>(p));
-}
-
-template <> struct WFrag<8> {
-  u32x4 q;
-  uint32_t sc;
-  // lane group g holds the 16 codes of columns [k0 + 16g, k0 + 16g + 16)
-  __device__ inline void load(const WRow<8>& r, int64_t k0) {
-    q = *gmem(reinterpret_cast<const u32x4*>(r.w + k0 + r.wo));
-    sc = load_scale(r.s + 2 * (k0 / kGroup) + r.so);
-  }
-  // bytes e0..e3 of a word, middle bytes swapped (e0 e2 e1 e3), pair as
-  // (e0,e1)(e2,e3) in column order, scaled
-  __device__ inline f16x8 get(int s) const {
-    const f16x2 bias = as_h2(0x64806480u);  // 1152 = 1024 + 128
-    const f16x2 s2 = splat_scale(sc);
-    uint32_t o[4];
+template <> struct Codes<8> {
+  static constexpr int kRaw = 2;  // 16-byte chunks of a lane's 32 codes
+  // bytes e0 e1 (e2 e3) of a word with 0x64 above each: 1024 + u
+  static __device__ inline f16x8 frag(const u32x4 (&q)[2], int s, f16x2 s2) {
+    u32x4 o;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const uint32_t w = __builtin_amdgcn_perm(q[2 * s + k], q[2 * s + k], 0x03010200u);
-      o[2 * k] = as_u32((as_h2((w & 0x00FF00FFu) | 0x64006400u) - bias) * s2);
-      o[2 * k + 1] = as_u32((as_h2(((w >> 8) & 0x00FF00FFu) | 0x64006400u) - bias) * s2);
+      const uint32_t w = q[s >> 1][(s & 1) * 2 + k];
+      o[2 * k] = scaled(__builtin_amdgcn_perm(0x64646464u, w, 0x04010400u), 0x64806480u, s2);
+      o[2 * k + 1] = scaled(__builtin_amdgcn_perm(0x64646464u, w, 0x04030402u), 0x64806480u, s2);
     }
-    return pack8(o[0], o[1], o[2], o[3]);
+    return __builtin_bit_cast(f16x8, o);
   }
 };
 
-template <> struct WFrag<4> {
-  u32x2 q;
-  uint32_t sc;
-  // lane group g holds the 16 codes of columns [k0 + 16g, k0 + 16g + 16)
-  __device__ inline void load(const WRow<4>& r, int64_t k0) {
-    q = *gmem(reinterpret_cast<const u32x2*>(r.w + k0 / 2 + r.wo));
-    sc = load_scale(r.s + 2 * (k0 / kGroup) + r.so);
-  }
-  // word with e0..e7 at bits 4j -> (e0,e4)(e1,e5)(e2,e6)(e3,e7), scaled
-  __device__ inline f16x8 get(int s) const {
-    const uint32_t w = s == 0 ? q.x : q.y;
-    const f16x2 bias = as_h2(0x64086408u);  // 1032 = 1024 + 8
-    const f16x2 s2 = splat_scale(sc);
-    uint32_t o[4];
+template <> struct Codes<4> {
+  static constexpr int kRaw = 1;
+  // byte b of the word (e2b, e2b+1) into bits 0..7 of both halves: u at
+  // bit 0 of the low half (1024 + 8), at bit 4 of the high half (64 + 8)
+  static __device__ inline f16x8 frag(const u32x4 (&q)[1], int s, f16x2 s2) {
+    const uint32_t w = q[0][s];
+    u32x4 o;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      o[k] = as_u32((as_h2(((w >> (4 * k)) & 0x000F000Fu) | 0x64006400u) - bias) * s2);
-    return pack8(o[0], o[1], o[2], o[3]);
-  }
-};
-
-template <> struct WFrag<2> {
-  uint32_t q;
-  uint32_t sc;
-  // lane group g holds the 16 codes of columns [k0 + 16g, k0 + 16g + 16)
-  __device__ inline void load(const WRow<2>& r, int64_t k0) {
-    q = *gmem(reinterpret_cast<const uint32_t*>(r.w + k0 / 4 + r.wo));
-    sc = load_scale(r.s + 2 * (k0 / kGroup) + r.so);
-  }
-  // half-word s holds e0..e7 at bits 2j; move byte 1 to byte 2 so that the
-  // mask 0x00030003 pairs (e_k, e_{k+4})
-  __device__ inline f16x8 get(int s) const {
-    const uint32_t w = q >> (16 * s);
-    const uint32_t v = (w & 0xFFu) | ((w & 0xFF00u) << 8);
-    const f16x2 bias = as_h2(0x64026402u);  // 1026 = 1024 + 2
-    const f16x2 s2 = splat_scale(sc);
-    uint32_t o[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      o[k] = as_u32((as_h2(((v >> (2 * k)) & 0x00030003u) | 0x64006400u) - bias) * s2);
-    return pack8(o[0], o[1], o[2], o[3]);
-  }
-};
-
-// One pass (up to kPassTok tokens) of one group over NM matrices:
-// acc[rt][tt][m] accumulates the tokens of tile tt against the weight rows
-// of tile rt.  Software pipeline over the stages k (64 columns each): the
-// weight fragments sit in a ring of WRING register slots (stage k in slot
-// k % WRING, reloaded with stage k + WRING as soon as its products are
-// issued; 2 slots for the up-projection, 3 for the down-projection) and
-// the activations of stage k + ADEPTH are fetched into register slot
-// k % ADEPTH right after stage k's barrier.  The memory
-// counter completes in order, so a weight load issued before an activation
-// fetch must also be complete when that activation is stored: the weights
-// get about ADEPTH stages to arrive, whatever the ring depth.  ADEPTH is 3
-// for the down-projection and 1 for the up-projection (2 fits in its
-// registers but measured no faster).  The stage loop is unrolled by kUnroll so that every ring index
-// is static: rotating register slots would copy registers whose loads are
-// still in flight, and make every stage wait for all of them.
-constexpr int kUnroll = 6;  // multiple of WRING (2, 3), ADEPTH (1, 3) and the 2 LDS buffers
-
-// Products of one stage, two token tiles at a time: the four fragments
-// of a tile pair (two tiles x two k-steps) are read from LDS together and
-// feed 4 * RT * NM products, ordered so that the products into one
-// accumulator are 2 * RT * NM apart (no stall on the previous result).  A
-// pair is computed whole when its first tile holds tokens: the second
-// tile's rows then repeat the pass's last token and are not stored.
-template <int BITS, int NM, int RT>
-__device__ inline void stage_mma(const f16* cur, const WFrag<BITS> (&w)[RT][NM], int ntile,
-                                 f32x4 (&acc)[RT][kTokTiles][NM]) {
-  static_assert(kTokTiles % 2 == 0, "tile pairs");
-  f16x8 b[kSteps][RT][NM];
-#pragma unroll
-  for (int s = 0; s < kSteps; ++s)
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int m = 0; m < NM; ++m) b[s][rt][m] = w[rt][m].get(s);
-#pragma unroll
-  for (int tp = 0; tp < kTokTiles; tp += 2) {
-    // pair 0 always holds a token: every path consumes the weight
-    // registers, so their reload needs no wait for an unconsumed load
-    if (tp == 0 || tp < ntile) {
-      f16x8 a[kSteps][2];
-#pragma unroll
-      for (int s = 0; s < kSteps; ++s)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) a[s][t] = a_frag<BITS>(cur, tp + t, s);
-#pragma unroll
-      for (int s = 0; s < kSteps; ++s)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int m = 0; m < NM; ++m)
-              acc[rt][tp + t][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                  a[s][t], b[s][rt][m], acc[rt][tp + t][m], 0, 0, 0);
+    for (int b = 0; b < 4; ++b) {
+      const uint32_t t = __builtin_amdgcn_perm(w, w, 0x0C000C00u + (uint32_t)b * 0x00010001u);
+      o[b] = scaled(__builtin_amdgcn_bitop3_b32(t, 0x00F0000Fu, 0x54006400u, kAndOr), 0x54806408u, s2);
     }
+    return __builtin_bit_cast(f16x8, o);
   }
+};
+
+template <> struct Codes<2> {
+  static constexpr int kRaw = 1;  // the lane's 8 bytes in the first half
+  // half-word s holds e0..e7; byte b (e4b .. e4b+3) into both halves: bits
+  // 0 / 2 (1024 + 2, 256 + 2), then bits 4 / 6 (64 + 2, 16 + 2)
+  static __device__ inline f16x8 frag(const u32x4 (&q)[1], int s, f16x2 s2) {
+    const uint32_t w = q[0][s >> 1];
+    u32x4 o;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const uint32_t t = __builtin_amdgcn_perm(w, w, 0x0C000C00u + (uint32_t)(2 * (s & 1) + b) * 0x00010001u);
+      o[2 * b] = scaled(__builtin_amdgcn_bitop3_b32(t, 0x000C0003u, 0x5C006400u, kAndOr), 0x5C086402u, s2);
+      o[2 * b + 1] = scaled(__builtin_amdgcn_bitop3_b32(t, 0x00C00030u, 0x4C005400u, kAndOr), 0x4C805420u, s2);
+    }
+    return __builtin_bit_cast(f16x8, o);
+  }
+};
+template <> struct Codes<16> { static constexpr int kRaw = 1; };
+
+// A wave-uniform pointer in scalar registers.
+__device__ inline const uint8_t* uniform(const void* p) {
+  const uint64_t v = (uint64_t)(uintptr_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const uint8_t*>(((uint64_t)hi << 32) | lo);
 }
 
-template <int BITS, int M0, int NM, int RT, int ADEPTH, int WRING>
-__device__ void gemm_pass(const ExpertEntry& ex, int64_t wrow0, int64_t ld,
-                          const f16* act, int64_t act_ld, const int32_t* perm,
-                          int off, int j0, int n, int K, bool gather, f16* lds,
-                          f32x4 (&acc)[RT][kTokTiles][NM]) {
-  static_assert(NM == 1 || NM == 2, "one or two matrices");
-  static_assert(kUnroll == 6 && kUnroll % WRING == 0 && kUnroll % ADEPTH == 0, "ring");
+template <class T>
+__device__ inline T lds_read(const lds_u8* lds, uint32_t at) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) T*>(lds + at);
+}
+
+// The two 128-row sub-blocks of a tile: W1 and W3 at the same rows, or two
+// consecutive 128-row blocks of W2; rows past `rows` repeat the last one.
+struct Sub {
+  const uint8_t *w0, *w1;
+  const uint8_t *s0, *s1;
+  int rows0, rows1;  // rows left in the matrix from the sub-block's first
+};
+
+// acc[i][t] (C tile: 32 weight rows x 32 tokens) of the wave's weight tile
+// i (tiles 0, 1: sub-block 0; 2, 3: sub-block 1) and token tile t, over all
+// of the ld columns.  act: row 0 of the block's activations (gather: x,
+// whose rows are perm[...] / K); n tokens.
+template <int BITS, int RT, int MT, bool GATHER>
+__device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act,
+                                          const int32_t* perm, int n, int K, lds_u8* lds,
+                                          f32x16 (&acc)[RT][MT]) {
+  using R = Ring<BITS, RT, MT>;
   const int l = threadIdx.x & 63;
-  const int ntile = (n + 15) >> 4;
-  const int64_t nst = ld / kStageK;  // ld is a multiple of kStageK
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+  const int nst = ld / kStageK;
+  const uint32_t row_bytes = (uint32_t)(ld * BITS / 8);
+  // load q of a slot covers rows 8 q + l / 8, and position l % 8 of a row
+  // holds chunk (l % 8) ^ ((row / 2) % 8); a wave's loads are q = wave + 4 i,
+  // so that row / 2 % 8 is 4 (wave % 2) + l / 16
+  const uint32_t chunk = 16 * ((l & 7) ^ (4 * (wave & 1) + (l >> 4)));
+  // rows of 64 bytes: row 16 q + l / 4, chunk (l % 4) ^ ((row / 4) % 4)
+  const uint32_t chunk64 = 16 * ((l & 3) ^ ((l >> 4) & 3));
+
+  uint32_t aoff[R::kALoads];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int tt = 0; tt < kTokTiles; ++tt)
-#pragma unroll
-      for (int m = 0; m < NM; ++m) acc[rt][tt][m] = f32x4{0, 0, 0, 0};
-  WRow<BITS> src[RT][NM];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int64_t row = wrow0 + rt * 16 + (l & 15);
-    src[rt][0] = wrow<BITS, M0>(ex, row, ld);
-    if constexpr (NM == 2) src[rt][1] = wrow<BITS, M0 + 1>(ex, row, ld);
+  for (int i = 0; i < R::kALoads; ++i) {
+    const int r = min(8 * (wave + 4 * i) + (l >> 3), n - 1);
+    const uint32_t src = GATHER ? (uint32_t)(perm[r] / K) : (uint32_t)r;
+    aoff[i] = src * (uint32_t)(2 * ld) + chunk;
   }
-  // ring slots past the last stage (never multiplied) reload the last
-  // stage, which the ring loaded a few stages before and L2 still holds
-  // (stage 0 would come from HBM again): unconditional loads, see ActStager
-  auto load_w = [&](WFrag<BITS> (&w)[RT][NM], int64_t k) {
-    const int64_t kc = (k < nst ? k : nst - 1) * kStageK;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int m = 0; m < NM; ++m) w[rt][m].load(src[rt][m], kc);
+  const uint8_t* abase = uniform(act);
+  // load i of the activations of stage k
+  auto load_a = [&](int k, int i, uint32_t slot) {
+    lds_load16(lds0 + slot * R::kASlot + (wave + 4 * i) * 1024, abase + (size_t)min(k, nst - 1) * 128,
+               aoff[i]);
   };
-  ActStager st;
-  st.init(act, act_ld, perm, off, j0, n, K, gather);
-  st.fetch<0>(act_ld, 0);
-  if (ADEPTH >= 2) st.fetch<1>(act_ld, kStageK);
-  if (ADEPTH >= 3) st.fetch<2>(act_ld, 2 * kStageK);
-  // issue order as in the loop (activations, then weights), so that the
-  // wait before the first store is the loop's
-  __builtin_amdgcn_sched_barrier(0);
-  WFrag<BITS> w[WRING][RT][NM];
+  // load i of unit u of the weights, the first half of them sub-block 0.  A
+  // code row whose last unit is partial reads its first chunk instead.
+  auto load_w = [&](int u, int i, uint32_t slot) {
+    constexpr int kPer = R::kRowBytes == 128 ? 8 : 16;  // rows per load
+    const bool second = i >= R::kWUnitLoads / 2;
+    const int r0 = kPer * (wave + 4 * (i % (R::kWUnitLoads / 2))) + (l * kPer >> 6);
+    const int r = min(r0, (second ? sub.rows1 : sub.rows0) - 1);
+    const uint32_t c0 = (uint32_t)u * R::kRowBytes + (BITS == 16 ? chunk : chunk64);
+    const uint32_t c = c0 < row_bytes ? c0 : 0;
+    lds_load16(lds0 + R::kWBase + slot * R::kWSlot + (wave + 4 * i) * 1024, second ? sub.w1 : sub.w0,
+               (uint32_t)r * row_bytes + c);
+  };
+  // load p of scale unit v: dword 4 v + l % 4 (two groups each) of rows
+  // 64 p + 16 wave + l / 4
+  auto load_s = [&](int v, int p, uint32_t slot) {
+    const bool second = p >= RT / 2;
+    const int r = min(64 * (p % (RT / 2)) + 16 * wave + (l >> 2), (second ? sub.rows1 : sub.rows0) - 1);
+    const int dw = min(4 * v + (l & 3), ld / 64 - 1);
+    lds_load4(lds0 + R::kSBase + slot * R::kSSlot + p * 1024 + wave * 256, second ? sub.s1 : sub.s0,
+              (uint32_t)r * (uint32_t)(ld / 16) + 4 * dw);
+  };
+
+  // the rings' first stages; the loads that the first stage needs come first
 #pragma unroll
-  for (int u = 0; u < WRING; ++u) load_w(w[u], u);
-  // one stage; u = k % kUnroll is a compile-time constant.  The stages of
-  // the main loop are unconditional: a skippable stage would let the
-  // compiler assume its loads missing and wait for every load in flight
-  // (the tail, under kUnroll stages, accepts that).
-  auto stage = [&](int64_t k, auto uc) {
-    constexpr int u = decltype(uc)::value;
-    constexpr int kSlot = u % ADEPTH;
-    // the buffer written here was last read two stages ago, before the
-    // previous stage's barrier
-    f16* cur = lds + (u & 1) * (kPassTok * kLdsRow);
-    st.store<kSlot, kPermuted<BITS>>(cur);
-    __syncthreads();
-    st.fetch<kSlot>(act_ld, (k + ADEPTH) * kStageK);
-    stage_mma<BITS, NM, RT>(cur, w[u % WRING], ntile, acc);
-    load_w(w[u % WRING], k + WRING);
-    // keep stages apart: scheduled across stages, the loads and fragment
-    // reads of later stages stretch the registers' live ranges
+  for (int v = 0; v < R::kWSlots - 1; ++v) {
+#pragma unroll
+    for (int p = 0; p < R::kSUnitLoads; ++p) load_s(v, p, v);
+#pragma unroll
+    for (int i = 0; i < R::kWUnitLoads; ++i) load_w(BITS == 16 ? min(v, nst - 1) : v, i, v);
+  }
+#pragma unroll
+  for (int v = 0; v < R::kASlots - 1; ++v)
+#pragma unroll
+    for (int i = 0; i < R::kALoads; ++i) load_a(v, i, v);
+
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][t][v] = 0.0f;
+
+  const int half = l >> 5;
+  const int sw = (l >> 1) & 7, sw64 = (l >> 2) & 3;              // chunk swizzles of this lane's rows
+  const uint32_t arow = (uint32_t)((wave & 1) * (32 * MT) + (l & 31)) * 128;   // token tile 0
+  const uint32_t wrow = (uint32_t)((wave >> 1) * (16 * RT) + (l & 31));        // weight tile 0
+  uint32_t cat[4];  // position of the lane's chunk of each step
+#pragma unroll
+  for (int s = 0; s < 4; ++s) cat[s] = 16 * ((4 * half + s) ^ sw);
+  // row of weight tile i relative to tile 0
+  auto tile_row = [](int i) { return (uint32_t)(i % (RT / 2) * 32 + i / (RT / 2) * R::kSubRows); };
+
+  f16x8 a[2][MT], b[2][RT];
+  u32x4 q[RT][Codes<BITS>::kRaw];
+  f16x2 s2[RT];
+  // Fragments of step s of the stage whose slots (and place j in its unit)
+  // are given; raw codes and scales are read with step 0.
+  auto read_a = [&](int s, int t, uint32_t as) {
+    a[s & 1][t] = lds_read<f16x8>(lds, as * R::kASlot + arow + cat[s] + t * 32 * 128);
+  };
+  auto read_q = [&](int i, int k, uint32_t ws, uint32_t ss) {
+    const uint32_t at = R::kWBase + ws * R::kWSlot + (wrow + tile_row(i)) * R::kRowBytes;
+    const uint32_t j = (uint32_t)k % R::kUnit;
+    if constexpr (BITS == 8) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) q[i][h] = lds_read<u32x4>(lds, at + 16 * ((2 * half + h) ^ sw64));
+    } else if constexpr (BITS == 4) {
+      q[i][0] = lds_read<u32x4>(lds, at + 16 * ((2 * j + half) ^ sw64));
+    } else if constexpr (BITS == 2) {
+      const u32x2 v = lds_read<u32x2>(lds, at + 16 * (j ^ sw64) + 8 * half);
+      q[i][0] = u32x4{v.x, v.y, 0, 0};
+    }
+    if constexpr (BITS != 16) {
+      const uint32_t sc = lds_read<uint16_t>(lds, R::kSBase + ss * R::kSSlot + (wrow + tile_row(i)) * 16 +
+                                                      2 * (2 * ((uint32_t)k % kScaleStages) + half));
+      s2[i] = as_h2(__builtin_amdgcn_perm(sc, sc, 0x01000100u));
+    }
+  };
+  auto read_w = [&](int s, int i, uint32_t ws) {
+    if constexpr (BITS == 16)
+      b[s & 1][i] = lds_read<f16x8>(lds, R::kWBase + ws * R::kWSlot + (wrow + tile_row(i)) * 128 + cat[s]);
+    else
+      b[s & 1][i] = Codes<BITS>::frag(q[i], s, s2[i]);
+  };
+  auto next = [](uint32_t slot, int slots) { return slot + 1 == (uint32_t)slots ? 0u : slot + 1; };
+  // quarter c of the products of step s
+  auto products = [&](int s, int c) {
+#pragma unroll
+    for (int m = c * RT * MT / 4; m < (c + 1) * RT * MT / 4; ++m)
+      acc[m % RT][m / RT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b[s & 1][m % RT], a[s & 1][m / RT],
+                                                                   acc[m % RT][m / RT], 0, 0, 0);
+  };
+  // keeps a quarter's reads and conversions between its products
+  auto pin = [&](auto reads, auto valu) {
+    constexpr int kM = RT * MT < 4 ? 1 : RT * MT / 4;
+#pragma unroll
+    for (int i = 0; i < kM; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+      __builtin_amdgcn_sched_group_barrier(0x100, (decltype(reads)::value + kM - 1) / kM, 0);  // LDS read
+      __builtin_amdgcn_sched_group_barrier(0x002, (decltype(valu)::value + kM - 1) / kM, 0);   // VALU
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
-  using I4 = std::integral_constant<int, 4>;
-  using I5 = std::integral_constant<int, 5>;
-  int64_t k0 = 0;
-  for (; k0 + kUnroll <= nst; k0 += kUnroll) {
-    stage(k0, I0{}); stage(k0 + 1, I1{}); stage(k0 + 2, I2{});
-    stage(k0 + 3, I3{}); stage(k0 + 4, I4{}); stage(k0 + 5, I5{});
-  }
-  // the last nst - k0 < kUnroll stages
-  const int64_t r = nst - k0;
-  if (r > 0) stage(k0, I0{});
-  if (r > 1) stage(k0 + 1, I1{});
-  if (r > 2) stage(k0 + 2, I2{});
-  if (r > 3) stage(k0 + 3, I3{});
-  if (r > 4) stage(k0 + 4, I4{});
-  __syncthreads();  // the LDS buffers are reused by the next pass
-}
+  using std::integral_constant;
 
-template <int BITS>
-__device__ __forceinline__ void up_group(const ExpertEntry& ex, const Group& g, const int32_t* perm,
-                         const f16* x, f16* h, int d, int f, int K, int tile, f16* lds) {
-  constexpr int RT = kUpRowsW / 16;
-  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t wrow0 = (int64_t)tile * kWaves * kUpRowsW + wave * kUpRowsW;
-  for (int j0 = 0; j0 < g.count; j0 += kPassTok) {
-    const int n = min(kPassTok, g.count - j0);
-    f32x4 acc[RT][kTokTiles][2];
-    gemm_pass<BITS, 0, 2, RT, 1, 2>(ex, wrow0, d, x, d, perm, g.offset, j0, n, K, true, lds, acc);
+  uint32_t as = 0, ws = 0, ss = 0;                                         // slots of stage k
+  uint32_t al = R::kASlots - 1, wl = R::kWSlots - 1, sl = R::kWSlots - 1;  // slots loaded next
+  // Quarter c's share of the loads of one stage, issued between the barrier
+  // before stage k and the one in it: weights and scales first.  Past the
+  // last stage they repeat it, so that the counts hold.
+  auto loads = [&](int k, int c) {
+    const int u = BITS == 16 ? min(k + R::kWSlots - 1, nst - 1) : k / R::kUnit + R::kWSlots - 1;
+    const int v = k / kScaleStages + R::kWSlots - 1;
+    const int j = k % R::kUnit, js = k % kScaleStages;
+    constexpr int kSpread = R::kWSlots == 2 ? 16 : 12;
+    // slots of a stage for weights and scales; where a unit has fewer loads
+    // than stages, every second stage has one
+    constexpr int kW = R::kWLoads > 0 ? R::kWLoads : 1;
+    constexpr int kS = BITS == 16 ? 0 : 1;
+    constexpr int kAll = kW + kS + R::kALoads;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int64_t row = wrow0 + rt * 16 + (l & 15);
+    for (int i = c * kAll / kSpread; i < min((c + 1) * kAll / kSpread, kAll); ++i) {
+      if (i < kW) {
+        if (R::kWLoads > 0) load_w(u, j * R::kWLoads + i, wl);
+        else if (j & 1) load_w(u, j >> 1, wl);
+      } else if (i < kW + kS) {
+        if (R::kSLoads > 0) load_s(v, js, sl);
+        else if (js & 1) load_s(v, js >> 1, sl);
+      } else {
+        load_a(k + R::kASlots - 1, i - kW - kS, al);
+      }
+    }
+  };
+
+  // (deeper rings wait for all: their counts hold from the loop's loads on)
+  stage_barrier<R::kASlots == 3 ? R::kALoads : 0>();
 #pragma unroll
-      for (int tt = 0; tt < kTokTiles; ++tt)
+  for (int i = 0; i < RT; ++i) {
+    read_q(i, 0, ws, ss);
+    read_w(0, i, ws);
+  }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int j = tt * 16 + 4 * (l >> 4) + i;
-          if (j < n && row < f) {
-            const float a = acc[rt][tt][0][i], b = acc[rt][tt][1][i];
-            h[(int64_t)(g.offset + j0 + j) * f + row] = (f16)(a / (1.0f + expf(-a)) * b);
-          }
+  for (int t = 0; t < MT; ++t) read_a(0, t, as);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) loads(0, c);
+  for (int k = 0; k < nst; ++k) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        loads(k, 4 + 4 * s + c);
+        // LDS reads in the first half of the step, two quarters before use
+        if (c < 2) {
+#pragma unroll
+          for (int t = c * MT / 2; t < (c + 1) * MT / 2; ++t) read_a(s + 1, t, as);
+          if (BITS == 16)
+#pragma unroll
+            for (int i = c * RT / 2; i < (c + 1) * RT / 2; ++i) read_w(s + 1, i, ws);
         }
+        if (BITS != 16)
+#pragma unroll
+          for (int i = c * RT / 4; i < (c + 1) * RT / 4; ++i) read_w(s + 1, i, ws);
+        products(s, c);
+        pin(integral_constant<int, 4>{}, integral_constant<int, BITS == 16 ? 8 : 20>{});
+      }
+    }
+    // every load of stage k + 1 has arrived; the slots of stage k are free
+    stage_barrier<R::kPending>();
+    as = next(as, R::kASlots);
+    al = next(al, R::kASlots);
+    if ((k + 1) % R::kUnit == 0) {
+      ws = next(ws, R::kWSlots);
+      wl = next(wl, R::kWSlots);
+    }
+    if ((k + 1) % kScaleStages == 0) {
+      ss = next(ss, R::kWSlots);
+      sl = next(sl, R::kWSlots);
+    }
+    // (after the last stage: reads that are not multiplied)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      loads(k + 1, c);
+      if (c < 2) {
+#pragma unroll
+        for (int i = c * RT / 2; i < (c + 1) * RT / 2; ++i) {
+          if (BITS != 16) read_q(i, k + 1, ws, ss);
+          else read_w(0, i, ws);
+        }
+#pragma unroll
+        for (int t = c * MT / 2; t < (c + 1) * MT / 2; ++t) read_a(0, t, as);
+      }
+      if (BITS != 16) {  // tile 0, tiles 1 and 2, tile 3; or tile 0, tile 1
+        if (c == 1 && RT == 4) read_w(0, 0, ws);
+        if (c == 2) read_w(0, RT == 4 ? 1 : 0, ws);
+        if (c == 2 && RT == 4) read_w(0, 2, ws);
+        if (c == 3) read_w(0, RT - 1, ws);
+      }
+      products(3, c);
+      pin(integral_constant<int, BITS == 16 ? 4 : 8>{}, integral_constant<int, BITS == 16 ? 8 : 36>{});
     }
   }
+  // the LDS must not be handed on with loads in flight
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// Work items are (group, row tile) in group-major order.  The hardware
-// hands consecutive blocks to the 8 XCDs in turn (block b to XCD b % 8), so
-// block b takes item (b % 8) * per + b / 8, per = ceil(items / 8): each XCD
-// runs one contiguous eighth of the items, i.e. the tiles of one or two
-// groups, whose gathered activation rows then sit in that XCD's L2 only
-// instead of being fetched by all eight (up- and down-projection of the
-// 512-token Mixtral-shaped stack: 21.2 -> 20.9 ms per pass).
-__device__ inline bool xcd_item(int n_groups, int n_tiles, int& gi, int& tile) {
-  const int total = n_groups * n_tiles, per = (total + 7) >> 3;
-  const int slot = blockIdx.x >> 3, item = (blockIdx.x & 7) * per + slot;
-  if (slot >= per || item >= total) return false;
-  gi = item / n_tiles;
-  tile = item - gi * n_tiles;
+// a / (1 + e^-a) on the exponential and reciprocal units (1 ulp each): the
+// result is rounded to fp16 next, and the full-range expf and division took
+// a tenth of the up-projection's time.  e^-a overflows to infinity for
+// a < -88 and the quotient then is -0, as in the exact form.
+__device__ inline float silu(float a) {
+  return a * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * a));
+}
+
+// Work item of a block: a group's token tile and a row tile.  Items are
+// listed in two runs: first the tiles of all groups that take the largest
+// block (more than 192 tokens), then the smaller remainders, so that the
+// small ones fill the last round.  Inside a group, up to kSuper token tiles
+// alternate fastest: the blocks that run together on an XCD share weight
+// rows and token rows.  The hardware hands block b to XCD b % 8: whole sets
+// of 256 items (one per compute unit) go to the XCDs in runs of 32, what is
+// left in eighths, so that every XCD gets the same mix of copies.
+struct Item {
+  Group g;
+  int tok0, tile;
+};
+constexpr int kSuper = 8;
+
+// Inclusive sum over the lanes up to this one (DPP row shifts, then the row
+// ends broadcast to the rows above).
+template <int CTRL, int ROWS>
+__device__ inline int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+__device__ inline int wave_scan(int v) {
+  v = dpp_add<0x111, 0xF>(v);  // row_shr:1
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+}
+
+// Slots per XCD for n items, and the item of an XCD's slot (-1: none).
+__device__ inline int xcd_slots(int n) { return (n >> 8) * 32 + (((n & 255) + 7) >> 3); }
+__device__ inline int xcd_item(int n, int xcd, int slot) {
+  const int sets = n >> 8, left = n & 255, per = (left + 7) >> 3;
+  if (slot < 32 * sets) return (slot >> 5) * 256 + xcd * 32 + (slot & 31);
+  const int q = slot - 32 * sets, item = xcd * per + q;
+  return q < per && item < left ? 256 * sets + item : -1;
+}
+
+__device__ inline bool take_item(const WorkList* wl, int n_tiles, Item& it) {
+  // Lane l takes groups 2 l and 2 l + 1; entries past the list hold stale
+  // groups and count nothing.  One memory round trip: the block's group is
+  // read from the lane that holds it.
+  const int lane = threadIdx.x & 63;
+  const u32x4 g0 = reinterpret_cast<const u32x4*>(wl->groups)[2 * lane];
+  const u32x4 g1 = reinterpret_cast<const u32x4*>(wl->groups)[2 * lane + 1];
+  const int ng = wl->n_groups;
+  const int cnt0 = 2 * lane < ng ? (int)g0.w : 0, cnt1 = 2 * lane + 1 < ng ? (int)g1.w : 0;
+  const int rem0 = cnt0 % kTileTok, rem1 = cnt1 % kTileTok;
+  const int big0 = cnt0 / kTileTok + (rem0 > 192), big1 = cnt1 / kTileTok + (rem1 > 192);
+  const int rest0 = rem0 > 0 && rem0 <= 192, rest1 = rem1 > 0 && rem1 <= 192;
+  // token tiles of both runs in one scan (at most 2^16 / 256 and 128)
+  const int scan = wave_scan((big0 + big1) | (rest0 + rest1) << 16);
+  const int all = __builtin_amdgcn_readlane(scan, 63);
+  const int n_big = (all & 0xFFFF) * n_tiles, n_rest = (all >> 16) * n_tiles;
+  const int slot = blockIdx.x >> 3, xcd = blockIdx.x & 7;
+  const int per_big = xcd_slots(n_big);
+  const bool small = slot >= per_big;
+  const int item = small ? xcd_item(n_rest, xcd, slot - per_big) : xcd_item(n_big, xcd, slot);
+  if (item < 0) return false;
+  const int upto = small ? scan >> 16 : scan & 0xFFFF;  // token tiles up to this lane's groups
+  const int own0 = small ? rest0 : big0, own1 = small ? rest1 : big1;
+  const int gl = __ffsll((unsigned long long)__ballot(upto * n_tiles > item)) - 1;
+  const int o0 = __builtin_amdgcn_readlane(own0, gl), o1 = __builtin_amdgcn_readlane(own1, gl);
+  int in = item - (__builtin_amdgcn_readlane(upto, gl) - o0 - o1) * n_tiles;
+  const bool odd = in >= o0 * n_tiles;
+  if (odd) in -= o0 * n_tiles;
+  const u32x4 g = odd ? g1 : g0;
+  it.g.expert = __builtin_amdgcn_readlane((int)g.x, gl);
+  it.g.bits = __builtin_amdgcn_readlane((int)g.y, gl);
+  it.g.offset = __builtin_amdgcn_readlane((int)g.z, gl);
+  it.g.count = __builtin_amdgcn_readlane((int)g.w, gl);
+  const int tt = odd ? o1 : o0;  // the group's token tiles in this run
+  const int sup = in / (kSuper * n_tiles), left = in - sup * (kSuper * n_tiles);
+  const int width = min(kSuper, tt - sup * kSuper);
+  it.tile = left / width;
+  const int t = sup * kSuper + left - it.tile * width;
+  it.tok0 = (small ? it.g.count / kTileTok : t) * kTileTok;
   return true;
 }
+static_assert(sizeof(Group) == 16 && offsetof(WorkList, groups) % 16 == 0 && kMaxKeys == 128,
+              "two groups per lane");
 
-__global__ __launch_bounds__(kThreads, 2) void prefill_up_kernel(
-    const ExpertEntry* __restrict__ table, const WorkList* __restrict__ wl,
-    const int32_t* __restrict__ perm, const f16* __restrict__ x, f16* __restrict__ h,
-    int d, int f, int K, int n_tiles) {
-  __shared__ f16 lds[2 * kPassTok * kLdsRow];
-  int gi, tile;
-  if (!xcd_item(wl->n_groups, n_tiles, gi, tile)) return;
-  const Group g = wl->groups[gi];
-  const ExpertEntry ex = table[g.expert];
-  if (g.bits == 16) up_group<16>(ex, g, perm, x, h, d, f, K, tile, lds);
-  else if (g.bits == 8) up_group<8>(ex, g, perm, x, h, d, f, K, tile, lds);
-  else if (g.bits == 4) up_group<4>(ex, g, perm, x, h, d, f, K, tile, lds);
-  else up_group<2>(ex, g, perm, x, h, d, f, K, tile, lds);
+// First row `row` of matrix M: weights (codes) and scales.
+template <int BITS, int M>
+__device__ inline const uint8_t* weights_at(const ExpertEntry& ex, int64_t row, int64_t ld) {
+  const uint8_t* w = BITS == 16 ? reinterpret_cast<const uint8_t*>(ex.w[M]) : BITS == 8 ? ex.hq[M] : ex.q[M];
+  return uniform(w + row * (ld * BITS / 8));
+}
+template <int BITS, int M>
+__device__ inline const uint8_t* scales_at(const ExpertEntry& ex, int64_t row, int64_t ld) {
+  if (BITS == 16) return nullptr;
+  return uniform((BITS == 8 ? ex.hs[M] : ex.s[M]) + row * (ld / kGroup));
 }
 
-// RT 16-row tiles of W2 per wave, each activation fragment read from LDS
-// serving all of them
-template <int BITS, int RT>
-__device__ __forceinline__ void down_group(const ExpertEntry& ex, const Group& g, const f16* h,
-                           float* e, int d, int f, int tile, f16* lds) {
+template <int BITS, int RT, int MT>
+__device__ __forceinline__ void up_tile(const ExpertEntry& ex, const Item& it, const int32_t* perm,
+                                        const f16* x, f16* h, int d, int f, int K, lds_u8* lds) {
+  const int n = min(kTileTok, it.g.count - it.tok0);
+  const int64_t row0 = (int64_t)it.tile * (32 * RT);
+  const Sub sub = {weights_at<BITS, 0>(ex, row0, d), weights_at<BITS, 1>(ex, row0, d),
+                   scales_at<BITS, 0>(ex, row0, d), scales_at<BITS, 1>(ex, row0, d),
+                   f - (int)row0, f - (int)row0};
+  f32x16 acc[RT][MT];
+  const int off = it.g.offset + it.tok0;
+  tile_gemm<BITS, RT, MT, true>(sub, d, x, perm + off, n, K, lds, acc);
   const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t wrow0 = (int64_t)(tile * kWaves + wave) * (16 * RT);
-  for (int j0 = 0; j0 < g.count; j0 += kPassTok) {
-    const int n = min(kPassTok, g.count - j0);
-    f32x4 acc[RT][kTokTiles][1];
-    gemm_pass<BITS, 2, 1, RT, 3, 3>(ex, wrow0, f, h, f, nullptr, g.offset, j0, n, 1, false, lds, acc);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int64_t row = wrow0 + rt * 16 + (l & 15);
+  for (int c = 0; c < RT / 2; ++c) {
+    const int64_t row = row0 + (wave >> 1) * (16 * RT) + c * 32;
+    if (row >= f) continue;
 #pragma unroll
-      for (int tt = 0; tt < kTokTiles; ++tt)
+    for (int t = 0; t < MT; ++t) {
+      const int j = (wave & 1) * (32 * MT) + 32 * t + (l & 31);
+      if (j < n) {
+        f16* out = h + (int64_t)(off + j) * f + row + 4 * (l >> 5);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int j = tt * 16 + 4 * (l >> 4) + i;
-          if (j < n && row < d) e[(int64_t)(g.offset + j0 + j) * d + row] = acc[rt][tt][0][i];
+        for (int q = 0; q < 4; ++q) {
+          f16x4 v;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float a = acc[c][t][4 * q + i], b = acc[c + RT / 2][t][4 * q + i];
+            v[i] = (f16)(silu(a) * b);
+          }
+          *reinterpret_cast<f16x4*>(out + 8 * q) = v;
         }
+      }
     }
   }
 }
 
-// RT = 2 (32 rows per wave, 128 per block) when d_model allows it: twice
-// the products per LDS fragment read, at one block of 4 waves per compute
-// unit with up to 512 registers each (down-projection of a Mixtral-shaped
-// 512-token layer 284 -> 256 us against RT = 1 at two blocks per unit).
+template <int BITS, int RT, int MT>
+__device__ __forceinline__ void down_tile(const ExpertEntry& ex, const Item& it, const f16* h,
+                                          float* e, int d, int f, lds_u8* lds) {
+  const int n = min(kTileTok, it.g.count - it.tok0);
+  const int row0 = it.tile * (64 * RT);
+  // a tile whose second half lies past the matrix reads the first half's rows
+  const int row1 = row0 + 32 * RT < d ? row0 + 32 * RT : row0;
+  const Sub sub = {weights_at<BITS, 2>(ex, row0, f), weights_at<BITS, 2>(ex, row1, f),
+                   scales_at<BITS, 2>(ex, row0, f), scales_at<BITS, 2>(ex, row1, f),
+                   d - row0, d - row1};
+  f32x16 acc[RT][MT];
+  const int64_t off = it.g.offset + it.tok0;
+  tile_gemm<BITS, RT, MT, false>(sub, f, h + off * f, nullptr, n, 1, lds, acc);
+  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const int rw = row0 + i / (RT / 2) * (32 * RT) + (wave >> 1) * (16 * RT) + i % (RT / 2) * 32;
+    if (rw >= d) continue;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int j = (wave & 1) * (32 * MT) + 32 * t + (l & 31);
+      if (j < n) {
+        float* out = e + (off + j) * d + rw + 4 * (l >> 5);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4*>(out + 8 * q) =
+              f32x4{acc[i][t][4 * q], acc[i][t][4 * q + 1], acc[i][t][4 * q + 2], acc[i][t][4 * q + 3]};
+      }
+    }
+  }
+}
+
+template <int BITS, int RT>
+__device__ __forceinline__ void up_item(const ExpertEntry& ex, const Item& it, const int32_t* perm,
+                                        const f16* x, f16* h, int d, int f, int K, lds_u8* lds) {
+  const int n = it.g.count - it.tok0;
+  if (n > 192) up_tile<BITS, RT, 4>(ex, it, perm, x, h, d, f, K, lds);
+  else if (n > 128) up_tile<BITS, RT, 3>(ex, it, perm, x, h, d, f, K, lds);
+  else if (n > 64) up_tile<BITS, RT, 2>(ex, it, perm, x, h, d, f, K, lds);
+  else up_tile<BITS, RT, 1>(ex, it, perm, x, h, d, f, K, lds);
+}
+
+template <int BITS, int RT>
+__device__ __forceinline__ void down_item(const ExpertEntry& ex, const Item& it, const f16* h,
+                                          float* e, int d, int f, lds_u8* lds) {
+  const int n = it.g.count - it.tok0;
+  if (n > 192) down_tile<BITS, RT, 4>(ex, it, h, e, d, f, lds);
+  else if (n > 128) down_tile<BITS, RT, 3>(ex, it, h, e, d, f, lds);
+  else if (n > 64) down_tile<BITS, RT, 2>(ex, it, h, e, d, f, lds);
+  else down_tile<BITS, RT, 1>(ex, it, h, e, d, f, lds);
+}
+
 template <int RT>
-__global__ __launch_bounds__(kThreads, RT == 2 ? 1 : 2) void prefill_down_kernel(
-    const ExpertEntry* __restrict__ table, const WorkList* __restrict__ wl,
-    const f16* __restrict__ h, float* __restrict__ e, int d, int f, int n_tiles) {
-  __shared__ f16 lds[2 * kPassTok * kLdsRow];
-  int gi, tile;
-  if (!xcd_item(wl->n_groups, n_tiles, gi, tile)) return;
-  const Group g = wl->groups[gi];
-  const ExpertEntry ex = table[g.expert];
-  if (g.bits == 16) down_group<16, RT>(ex, g, h, e, d, f, tile, lds);
-  else if (g.bits == 8) down_group<8, RT>(ex, g, h, e, d, f, tile, lds);
-  else if (g.bits == 4) down_group<4, RT>(ex, g, h, e, d, f, tile, lds);
-  else down_group<2, RT>(ex, g, h, e, d, f, tile, lds);
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void prefill_up_kernel(const ExpertEntry* __restrict__ table, const WorkList* __restrict__ wl,
+                            const int32_t* __restrict__ perm, const f16* __restrict__ x,
+                            f16* __restrict__ h, int d, int f, int K, int n_tiles) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kLdsBytes];
+  lds_u8* lds = (lds_u8*)smem;
+  Item it;
+  if (!take_item(wl, n_tiles, it)) return;
+  const ExpertEntry ex = table[it.g.expert];
+  if (it.g.bits == 16) up_item<16, RT>(ex, it, perm, x, h, d, f, K, lds);
+  else if (it.g.bits == 8) up_item<8, RT>(ex, it, perm, x, h, d, f, K, lds);
+  else if (it.g.bits == 4) up_item<4, RT>(ex, it, perm, x, h, d, f, K, lds);
+  else up_item<2, RT>(ex, it, perm, x, h, d, f, K, lds);
+}
+
+template <int RT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void prefill_down_kernel(const ExpertEntry* __restrict__ table, const WorkList* __restrict__ wl,
+                              const f16* __restrict__ h, float* __restrict__ e, int d, int f,
+                              int n_tiles) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kLdsBytes];
+  lds_u8* lds = (lds_u8*)smem;
+  Item it;
+  if (!take_item(wl, n_tiles, it)) return;
+  const ExpertEntry ex = table[it.g.expert];
+  if (it.g.bits == 16) down_item<16, RT>(ex, it, h, e, d, f, lds);
+  else if (it.g.bits == 8) down_item<8, RT>(ex, it, h, e, d, f, lds);
+  else if (it.g.bits == 4) down_item<4, RT>(ex, it, h, e, d, f, lds);
+  else down_item<2, RT>(ex, it, h, e, d, f, lds);
 }
 
 // One block per token; thread i owns the float4 pieces i, i + 1024, ... of
@@ -561,34 +737,56 @@ __global__ __launch_bounds__(kCombineThreads) void combine_prefill_kernel(
                                });
 }
 
+// Blocks for any work list: full token tiles of all the pairs and one
+// remainder per group, each run rounded up to whole eighths.
+int max_blocks(int T, int K, int max_groups, int n_tiles) {
+  return (((T * K / kTileTok + max_groups) * n_tiles + 7) / 8 + 1) * 8;
+}
+
+// Blocks of 256 weight rows where the step is expected to have enough of
+// them, of 128 rows otherwise.  The step's token tiles: one per group of
+// fewer than 256 tokens, half a tile more than its tokens fill otherwise.
+// The larger blocks read less from L2 and LDS per product, but fewer than
+// about 144 of them (9/16 of the 256 compute units) leave too much of the
+// chip idle.  Measured with 256 / 128 rows, half of the experts fp16 and
+// half int4: down-projection of the Mixtral-shaped layer at 512 tokens (128
+// larger blocks) 347 / 259 us, of the Phi-shaped one (256) 161 / 193 us;
+// up-projection at d 1024, f 2048, 8 experts, 512 tokens (128) 31 / 26 us,
+// 1024 tokens (192) 36 / 42 us; Mixtral-shaped at 64 tokens (896) 310 / 361.
+bool large_blocks(int T, int K, int E, int n_tiles) {
+  const int P = T * K, g = P < E ? P : E;
+  const int filled = P / kTileTok + g / 2;
+  return (int64_t)(filled > g ? filled : g) * n_tiles >= 144;
+}
+
 }  // namespace
 
-hipError_t launch_prefill_up(const ExpertEntry* table, const WorkList* wl,
-                             const int32_t* perm, const f16* x, f16* h, int T,
-                             int d, int f, int K, int max_groups, hipStream_t s) {
-  (void)T;
-  // whole stages and whole row tiles: every load stays inside the matrices
-  if (d % kStageK || f % (kWaves * kUpRowsW)) return hipErrorInvalidValue;
-  const int rows_per_block = kWaves * kUpRowsW;
-  const int n_tiles = (f + rows_per_block - 1) / rows_per_block;
-  prefill_up_kernel<<<(max_groups * n_tiles + 7) / 8 * 8, kThreads, 0, s>>>(table, wl, perm, x, h, d, f, K, n_tiles);
+hipError_t launch_prefill_up(const ExpertEntry* table, const WorkList* wl, const int32_t* perm,
+                             const f16* x, f16* h, int T, int d, int f, int E, int K,
+                             int max_groups, hipStream_t s) {
+  // whole stages and whole 32-row tiles
+  if (d % kStageK || f % 32) return hipErrorInvalidValue;
+  const int n_large = (f + 127) / 128, n_small = (f + 63) / 64;
+  if (large_blocks(T, K, E, n_large))
+    prefill_up_kernel<4><<<max_blocks(T, K, max_groups, n_large), kThreads, 0, s>>>(
+        table, wl, perm, x, h, d, f, K, n_large);
+  else
+    prefill_up_kernel<2><<<max_blocks(T, K, max_groups, n_small), kThreads, 0, s>>>(
+        table, wl, perm, x, h, d, f, K, n_small);
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_down(const ExpertEntry* table, const WorkList* wl,
-                               const f16* h, float* e, int T, int d, int f, int K,
-                               int max_groups, hipStream_t s) {
-  (void)T;
-  (void)K;
-  // whole stages and whole row tiles: every load stays inside the matrices
-  if (f % kStageK || d % (kWaves * 16)) return hipErrorInvalidValue;
-  if (d % (kWaves * 32) == 0) {
-    const int n_tiles = d / (kWaves * 32);
-    prefill_down_kernel<2><<<(max_groups * n_tiles + 7) / 8 * 8, kThreads, 0, s>>>(table, wl, h, e, d, f, n_tiles);
-  } else {
-    const int n_tiles = d / (kWaves * 16);
-    prefill_down_kernel<1><<<(max_groups * n_tiles + 7) / 8 * 8, kThreads, 0, s>>>(table, wl, h, e, d, f, n_tiles);
-  }
+hipError_t launch_prefill_down(const ExpertEntry* table, const WorkList* wl, const f16* h,
+                               float* e, int T, int d, int f, int E, int K, int max_groups,
+                               hipStream_t s) {
+  if (f % kStageK || d % 32) return hipErrorInvalidValue;
+  const int n_large = (d + 255) / 256, n_small = (d + 127) / 128;
+  if (large_blocks(T, K, E, n_large))
+    prefill_down_kernel<4><<<max_blocks(T, K, max_groups, n_large), kThreads, 0, s>>>(
+        table, wl, h, e, d, f, n_large);
+  else
+    prefill_down_kernel<2><<<max_blocks(T, K, max_groups, n_small), kThreads, 0, s>>>(
+        table, wl, h, e, d, f, n_small);
   return hipGetLastError();
 }
 

@@ -80,8 +80,8 @@ def test_prefill_tiny():
 
 
 def test_prefill_tiny_many_tokens_all_tags():
-    """Groups of more than one 160-token pass at every width (fp16, int4,
-    int2: about 210 tokens each); every tag kind."""
+    """Groups of about 210 tokens at every width (fp16, int4,
+    int2); every tag kind."""
     wl = _edge("prefill_busy", 41, 256, 512, 4, 2, 420,
                [C.TAG_FP16, C.TAG_INT4, C.TAG_INT2, C.TAG_MISS_INT4], t1=0.45, t2=1.0)
     rng = np.random.default_rng(11)
@@ -108,8 +108,8 @@ def test_prefill_skip_and_residual():
 
 def test_prefill_max_tokens():
     """The largest step a layer takes (8192 tokens): about 2,000 tokens per
-    group, i.e. 13 passes of 160 tokens per weight tile, every tag kind;
-    routing of all tokens, the output on 512 evenly spread tokens."""
+    group, i.e. 8 or 9 token tiles per weight tile, every tag kind; routing
+    of all tokens, the output on 512 evenly spread tokens."""
     T = 8192
     wl = _edge("prefill_max", 44, 256, 512, 8, 2, T,
                [C.TAG_FP16, C.TAG_INT4, C.TAG_INT2, C.TAG_MISS_INT4, C.TAG_MISS_INT2,
@@ -146,3 +146,31 @@ def test_prefill_matches_decode():
     L.destroy()
     assert np.array_equal(idx_p, idx_d) and np.array_equal(prec_p, prec_d)
     assert S.normwise(y_p, y_d).max() <= S.TOL
+
+
+# One expert, so that its group has exactly T tokens: the edges of the token
+# tiles (64, 128, 192 and 256 tokens per block and the next one), the number
+# of reduction stages from one (d 64) over fewer than the staging rings hold
+# to many, and weight rows that fill no tile.  d 1088 with 8192 tokens takes
+# the 256-row blocks in both projections, the others the 128-row ones.
+@pytest.mark.parametrize("tag", [C.TAG_FP16, C.TAG_INT8, C.TAG_INT4, C.TAG_INT2])
+@pytest.mark.parametrize("d,f,T", [(64, 64, 1), (64, 192, 64), (192, 64, 65), (320, 448, 128),
+                                   (576, 320, 129), (128, 704, 192), (448, 128, 193),
+                                   (832, 192, 256), (192, 832, 257), (320, 192, 513),
+                                   (1088, 704, 8192)])
+def test_prefill_tile_edges(tag, d, f, T):
+    wl = _edge(f"prefill_edge_{tag}_{d}_{f}_{T}", 45, d, f, 1, 1, T, [tag])
+    x = np.random.default_rng(15).standard_normal((T, d)).astype(np.float16)
+    sample = np.unique(np.linspace(0, T - 1, 600).astype(int))
+    _check(wl, wl.fixed_tags, x, sample=sample)
+
+
+@pytest.mark.parametrize("E,K,T", [(64, 8, 700), (64, 1, 8192), (3, 2, 4000)])
+def test_prefill_many_groups(E, K, T):
+    """Work lists of up to 128 groups (both copies of every expert), of groups
+    that are all small, and of few large ones with remainders."""
+    wl = _edge(f"prefill_groups_{E}_{K}_{T}", 46, 128, 192, E, K, T,
+               [(C.TAG_MISS_INT4, C.TAG_MISS_INT2, C.TAG_MISS_INT8_INT2)[e % 3] for e in range(E)],
+               t1=0.3, t2=0.9)
+    x = np.random.default_rng(16).standard_normal((T, 128)).astype(np.float16)
+    _check(wl, wl.fixed_tags, x, sample=np.unique(np.linspace(0, T - 1, 500).astype(int)))
