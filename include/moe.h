@@ -179,8 +179,8 @@ moe_status moe_decode_step_residual(moe_layer_t layer, int32_t n_tokens,
  * A stack of layers is one call per layer on the same h; the results equal
  * moe_rmsnorm followed by moe_decode_step_residual per layer, bit for bit,
  * with one launch fewer per layer (the router forms the norm when the
- * step's activations fit in its LDS: n_tokens * d_model <= 32768 and
- * d_model <= 4096).  Other arguments, limits and errors as
+ * step's activations fit in its LDS: n_tokens <= 8, n_tokens * d_model <=
+ * 32768 and d_model <= 4096).  Other arguments, limits and errors as
  * moe_decode_step. */
 moe_status moe_decode_step_prenorm(moe_layer_t layer, int32_t n_tokens, float* h,
                                    void* x, int32_t* topk_idx, float* topk_w,

@@ -17,9 +17,11 @@ namespace moe {
 namespace {
 
 constexpr int kRouteThreads = 1024;
+constexpr int kRouteSmallTokens = 8;  // tokens a step's single router block takes
 static_assert(kMaxExperts <= kRouteThreads, "one thread per expert stages the table");
-constexpr int kPrefillTokPerBlock = 1;
-constexpr int kPrefillThreads = 256;
+constexpr int kRouteWaves = kRouteThreads / 64;
+constexpr int kRowChunks = 8;     // 512-column chunks of a row held in registers at once
+constexpr int kMaxTokPerBlock = 16;
 
 // fp16-pair dot product with fp32 accumulation.  The operands are taken
 // as scalars on purpose: clang's __builtin_bit_cast applied directly to a
@@ -83,164 +85,14 @@ __device__ void gate_logits(const RouteParams& p, int t0, int t1, float* lg) {
   }
 }
 
-// top-k, softmax over the selected logits and the Eq. 2 rule for one token;
-// tags[e] is the expert table's tag column staged in LDS.
-__device__ void decide_token(const RouteParams& p, int t, const float* lrow,
-                             const int* tags, RouteOut o, int32_t* s_idx = nullptr,
-                             int8_t* s_prec = nullptr) {
-  int sel[kMaxTopK];
-  float ls[kMaxTopK];
-  uint64_t taken = 0;  // E <= 64
-  for (int k = 0; k < p.K; ++k) {
-    int best = -1;
-    float bv = 0.0f;
-    for (int e = 0; e < p.E; ++e) {
-      if (taken >> e & 1ull) continue;
-      const float v = lrow[e];
-      if (best < 0 || v > bv) {  // strict: exact ties keep the lower index
-        best = e;
-        bv = v;
-      }
-    }
-    taken |= 1ull << best;
-    sel[k] = best;
-    ls[k] = bv;
-  }
-  float ex[kMaxTopK];
-  float z = 0.0f;
-  for (int k = 0; k < p.K; ++k) {
-    ex[k] = expf(ls[k] - ls[0]);
-    z += ex[k];
-  }
-  float above = 0.0f;  // Eq. 2 running score
-  for (int k = 0; k < p.K; ++k) {
-    const float w = ex[k] / z;
-    const int e = sel[k];
-    const int tag = tags[e];
-    int prec;
-    if (tag == TAG_FP16 || tag == TAG_INT8) {
-      prec = PREC_HIGH;
-    } else if (tag == TAG_INT4 || tag == TAG_INT2) {
-      prec = PREC_LOW;
-    } else {
-      const float s = (k == 0) ? 0.0f : above;
-      prec = (k == 0 || s <= p.t1) ? PREC_HIGH
-                                   : (s <= p.t2 ? PREC_LOW : PREC_SKIP);
-    }
-    above += w;
-    const int pi = t * p.K + k;
-    o.idx[pi] = e;
-    o.w[pi] = w;
-    o.prec[pi] = (int8_t)prec;
-    if (s_idx) {
-      s_idx[pi] = e;
-      s_prec[pi] = (int8_t)prec;
-    }
-    if (o.user_idx) o.user_idx[pi] = e;
-    if (o.user_w) o.user_w[pi] = w;
-    if (o.user_prec) o.user_prec[pi] = (int8_t)prec;
-  }
-}
-
-// Stable counting sort of all T*K pairs by key = expert*2 + (low ? 1 : 0)
-// (skipped pairs get no key).  Run by one whole block of kRouteThreads.
 // Copy widths of one expert packed in one int: low copy (4, 2 or 0) in
 // bits 0-7, high copy (16 or 8) in bits 8-15.
 __device__ inline int pack_widths(const ExpertEntry& x) { return x.low_bits | (x.hi_bits << 8); }
 __device__ inline int copy_bits(int widths, int low) { return low ? (widths & 0xFF) : (widths >> 8); }
 
-// Pairs are taken one block-wide chunk at a time; inside a wave, lanes with
-// equal keys are found with one ballot per distinct key, and a lane's rank
-// among them is the number of lower lanes in that ballot; per-wave counts
-// are then scanned across waves, so pair order inside a group is the pair
-// index order.
-__device__ void build_worklist(const RouteParams& p, const int32_t* idx,
-                               const int8_t* prec, const int* widths,
-                               WorkList* wl, int32_t* perm, int32_t* pos) {
-  constexpr int kW = kRouteThreads / 64;
-  __shared__ int cnt[kMaxKeys];
-  __shared__ int base[kMaxKeys];
-  __shared__ int wcnt[kW][kMaxKeys];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int N = p.T * p.K;
-  const int n_keys = 2 * p.E;
-  for (int k = tid; k < n_keys; k += blockDim.x) cnt[k] = 0;
-  __syncthreads();
-  for (int i = tid; i < N; i += blockDim.x) {
-    const int pr = prec[i];
-    if (pr != PREC_SKIP) atomicAdd(&cnt[idx[i] * 2 + (pr == PREC_LOW)], 1);
-    else pos[i] = -1;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int off = 0, ng = 0, mx = 0;
-    for (int k = 0; k < n_keys; ++k) {
-      base[k] = off;
-      const int c = cnt[k];
-      if (c > 0) {
-        const int e = k >> 1;
-        Group g;
-        g.expert = e;
-        g.bits = copy_bits(widths[e], k & 1);
-        g.offset = off;
-        g.count = c;
-        wl->groups[ng++] = g;
-        mx = c > mx ? c : mx;
-      }
-      off += c;
-    }
-    wl->n_groups = ng;
-    wl->max_count = mx;
-  }
-  const uint64_t lower = (1ull << lane) - 1ull;
-  for (int c0 = 0; c0 < N; c0 += blockDim.x) {
-    for (int v = tid; v < kW * n_keys; v += blockDim.x) wcnt[v / n_keys][v % n_keys] = 0;
-    __syncthreads();
-    const int i = c0 + tid;
-    int key = -1;
-    if (i < N && prec[i] != PREC_SKIP) key = idx[i] * 2 + (prec[i] == PREC_LOW);
-    int rank = 0;
-    uint64_t todo = __ballot(key >= 0);
-    while (todo) {
-      const int leader = __ffsll((unsigned long long)todo) - 1;
-      const int k = __builtin_amdgcn_readlane(key, leader);
-      const uint64_t m = __ballot(key == k);
-      if (key == k) rank = __popcll(m & lower);
-      if (lane == leader) wcnt[wave][k] = __popcll(m);
-      todo &= ~m;
-    }
-    __syncthreads();
-    // exclusive scan of the per-wave counts, per key
-    if (tid < n_keys) {
-      int run = base[tid];
-      for (int w = 0; w < kW; ++w) {
-        const int c = wcnt[w][tid];
-        wcnt[w][tid] = run;
-        run += c;
-      }
-      base[tid] = run;
-    }
-    __syncthreads();
-    if (key >= 0) {
-      const int at = wcnt[wave][key] + rank;
-      perm[at] = i;
-      pos[i] = at;
-    }
-    __syncthreads();
-  }
-}
-
-// Expert tags and copy widths into LDS.
-__device__ inline void stage_table(const RouteParams& p, int* tags, int* widths) {
-  for (int e = threadIdx.x; e < p.E; e += blockDim.x) {
-    tags[e] = p.table[e].tag;
-    widths[e] = pack_widths(p.table[e]);
-  }
-}
-
-// The same in two halves: the loads are issued before the gate loads and
-// the LDS stores after them, so the two memory round trips overlap (E is at
-// most 64, below the block size).
+// One expert's tag and copy widths per thread (E is at most 64, below the
+// block size): the loads are issued before the gate loads and the LDS stores
+// come after them, so the two memory round trips overlap.
 struct TableRow {
   int tag, widths;
   __device__ inline void load(const RouteParams& p) {
@@ -337,78 +189,88 @@ __device__ inline uint32_t float_key(float v) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// top-k, softmax over the selected logits and the Eq. 2 rule for tokens
-// wave, wave + 16, ...: lanes are experts; slot k is the wave maximum of
-// (logit, -index) over the experts not yet taken, so exact ties keep the
-// lower index.  The softmax and the running Eq. 2 score are evaluated in
-// the same order as decide_token.
-__device__ void decide_wave(const RouteParams& p, const float* lg, const int* tags,
+// top-k, softmax over the selected logits and the Eq. 2 rule for token t by
+// one wave: lanes are experts; slot k is the wave maximum of (logit, -index)
+// over the experts not yet taken, so exact ties keep the lower index.  lrow:
+// the token's E logits in LDS; s_idx / s_prec: the pairs in LDS, or null.
+// A NaN logit: a decode step's router (FIRST = false) takes it as larger than
+// any number (smaller with the sign bit), a prefill's as one that is only
+// selected if no expert of a lower index is left.
+template <bool FIRST>
+__device__ void decide_wave(const RouteParams& p, int t, const float* lrow, const int* tags,
                             RouteOut o, int32_t* s_idx, int8_t* s_prec) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int kW = kRouteThreads / 64;
-  for (int t = wave; t < p.T; t += kW) {
-    float v = lane < p.E ? lg[t * p.E + lane] : -__builtin_inff();
-    int sel[kMaxTopK];
-    float ls[kMaxTopK];
+  const int lane = threadIdx.x & 63;
+  float v = lane < p.E ? lrow[lane] : -__builtin_inff();
+  int sel[kMaxTopK];
+  float ls[kMaxTopK];
+  uint64_t taken = 0;
 #pragma unroll
-    for (int k = 0; k < kMaxTopK; ++k) {
-      if (k >= p.K) break;
-      uint64_t key = ((uint64_t)float_key(v) << 32) | (uint32_t)(63 - lane);
-      if (lane >= p.E) key = 0;  // never selected (E >= K experts remain)
-#pragma unroll
-      for (int o_ = 32; o_ > 0; o_ >>= 1) {
-        const uint64_t other = __shfl_xor(key, o_, 64);
-        key = other > key ? other : key;
-      }
-      const int e = 63 - (int)(key & 63u);
-      sel[k] = e;
-      ls[k] = __shfl(v, e, 64);
-      if (lane == e) v = -__builtin_inff();
+  for (int k = 0; k < kMaxTopK; ++k) {
+    if (k >= p.K) break;
+    uint64_t key = ((uint64_t)float_key(v) << 32) | (uint32_t)(63 - lane);
+    if (FIRST) {
+      const int first = __ffsll((unsigned long long)~taken) - 1;
+      if (v != v) key = ((uint64_t)(lane == first ? 0xFFFFFFFFu : 0u) << 32) | (uint32_t)(63 - lane);
+      if (taken >> lane & 1) key = 0;
     }
-    float ex[kMaxTopK];
-    float z = 0.0f;
+    if (lane >= p.E) key = 0;  // never selected (E >= K experts remain)
 #pragma unroll
-    for (int k = 0; k < kMaxTopK; ++k) {
-      if (k < p.K) {
-        ex[k] = expf(ls[k] - ls[0]);
-        z += ex[k];
-      }
+    for (int o_ = 32; o_ > 0; o_ >>= 1) {
+      const uint64_t other = __shfl_xor(key, o_, 64);
+      key = other > key ? other : key;
     }
-    float above = 0.0f;  // Eq. 2 running score
+    const int e = 63 - (int)(key & 63u);
+    sel[k] = e;
+    ls[k] = __shfl(v, e, 64);
+    if (FIRST) taken |= 1ull << e;
+    else if (lane == e) v = -__builtin_inff();
+  }
+  float ex[kMaxTopK];
+  float z = 0.0f;
 #pragma unroll
-    for (int k = 0; k < kMaxTopK; ++k) {
-      if (k >= p.K) break;
-      const float w = ex[k] / z;
-      const int e = sel[k];
-      const int tag = tags[e];
-      int prec;
-      if (tag == TAG_FP16 || tag == TAG_INT8) {
-        prec = PREC_HIGH;
-      } else if (tag == TAG_INT4 || tag == TAG_INT2) {
-        prec = PREC_LOW;
-      } else {
-        const float sc = (k == 0) ? 0.0f : above;
-        prec = (k == 0 || sc <= p.t1) ? PREC_HIGH : (sc <= p.t2 ? PREC_LOW : PREC_SKIP);
-      }
-      above += w;
-      if (lane == k) {
-        const int pi = t * p.K + k;
-        o.idx[pi] = e;
-        o.w[pi] = w;
-        o.prec[pi] = (int8_t)prec;
+  for (int k = 0; k < kMaxTopK; ++k) {
+    if (k < p.K) {
+      ex[k] = expf(ls[k] - ls[0]);
+      z += ex[k];
+    }
+  }
+  float above = 0.0f;  // Eq. 2 running score
+#pragma unroll
+  for (int k = 0; k < kMaxTopK; ++k) {
+    if (k >= p.K) break;
+    const float w = ex[k] / z;
+    const int e = sel[k];
+    const int tag = tags[e];
+    int prec;
+    if (tag == TAG_FP16 || tag == TAG_INT8) {
+      prec = PREC_HIGH;
+    } else if (tag == TAG_INT4 || tag == TAG_INT2) {
+      prec = PREC_LOW;
+    } else {
+      const float sc = (k == 0) ? 0.0f : above;
+      prec = (k == 0 || sc <= p.t1) ? PREC_HIGH : (sc <= p.t2 ? PREC_LOW : PREC_SKIP);
+    }
+    above += w;
+    if (lane == k) {
+      const int pi = t * p.K + k;
+      o.idx[pi] = e;
+      o.w[pi] = w;
+      o.prec[pi] = (int8_t)prec;
+      if (s_idx) {
         s_idx[pi] = e;
         s_prec[pi] = (int8_t)prec;
-        if (o.user_idx) o.user_idx[pi] = e;
-        if (o.user_w) o.user_w[pi] = w;
-        if (o.user_prec) o.user_prec[pi] = (int8_t)prec;
       }
+      if (o.user_idx) o.user_idx[pi] = e;
+      if (o.user_w) o.user_w[pi] = w;
+      if (o.user_prec) o.user_prec[pi] = (int8_t)prec;
     }
   }
 }
 
-// The stable counting sort of build_worklist for at most 64 pairs, in one
-// wave: keys in increasing order, one ballot each; a pair's rank is the
-// number of lower lanes with the same key.
+// Work list of at most 64 pairs by one wave: a stable counting sort over the
+// keys (expert, precision), keys in increasing order, one ballot each; a
+// pair's rank is the number of lower lanes with the same key, so pair order
+// inside a group is the pair index order.  Skipped pairs get no key.
 __device__ void worklist_wave(const RouteParams& p, const int32_t* idx, const int8_t* prec,
                               const int* widths, WorkList* wl, int32_t* perm, int32_t* pos) {
   const int lane = threadIdx.x & 63;
@@ -448,13 +310,14 @@ __device__ void worklist_wave(const RouteParams& p, const int32_t* idx, const in
   }
 }
 
-// Decode: one block routes every token and builds the work list.
+// Steps of up to kRouteSmallTokens tokens: one block routes every token and
+// builds the work list.
 __global__ __launch_bounds__(kRouteThreads) void route_decode_kernel(
     RouteParams p, RouteOut o, WorkList* wl, int32_t* perm, int32_t* pos) {
-  __shared__ float lg[kDecodeMaxTokens * kMaxExperts];
+  __shared__ float lg[kRouteSmallTokens * kMaxExperts];
   __shared__ int tags[kMaxExperts], widths[kMaxExperts];
-  __shared__ int32_t s_idx[kDecodeMaxTokens * kMaxTopK];
-  __shared__ int8_t s_prec[kDecodeMaxTokens * kMaxTopK];
+  __shared__ int32_t s_idx[kRouteSmallTokens * kMaxTopK];
+  __shared__ int8_t s_prec[kRouteSmallTokens * kMaxTopK];
   __shared__ __attribute__((aligned(16))) f16 xs[kFastXBytes / 2];
   TableRow tr;
   tr.load(p);
@@ -465,57 +328,218 @@ __global__ __launch_bounds__(kRouteThreads) void route_decode_kernel(
   else gate_logits<4, 4>(p, 0, p.T, lg);
   tr.store(p, tags, widths);
   __syncthreads();
-  decide_wave(p, lg, tags, o, s_idx, s_prec);
+  for (int t = threadIdx.x >> 6; t < p.T; t += kRouteWaves)
+    decide_wave<false>(p, t, lg + t * p.E, tags, o, s_idx, s_prec);
   __syncthreads();
-  if (p.T * p.K <= 64) {
-    if (threadIdx.x < 64) worklist_wave(p, s_idx, s_prec, widths, wl, perm, pos);
+  static_assert(kRouteSmallTokens * kMaxTopK <= 64, "one pair per lane");
+  if (threadIdx.x < 64) worklist_wave(p, s_idx, s_prec, widths, wl, perm, pos);
+}
+
+// More tokens: blocks of TPB tokens each; a second kernel builds the list.
+// What bounds it is latency up to some hundred tokens (the single block took
+// 20 us at 16 tokens and 57 at 64, both kernels together take 12), then the
+// L2 reads of the gate, once per block: 8192 tokens, 16 experts 169 -> 97 us
+// for both kernels against one token per block.
+// With E <= 16 and d <= 4096 a wave keeps its expert's gate row in registers
+// for all of its tokens (the waves beyond the experts take other tokens);
+// the token rows are read by every expert's wave and hit L1.  One token per
+// block while that leaves compute units free: the call is then two memory
+// round trips and a launch.  Logits are summed over the chunks in the same
+// order as in the other routers.
+template <bool FIRST, int TPB>
+__global__ __launch_bounds__(kRouteThreads) void route_tokens_kernel(RouteParams p, RouteOut o) {
+  __shared__ float lg[TPB * kMaxExperts];
+  __shared__ int tags[kMaxExperts], widths[kMaxExperts];
+  const int t0 = blockIdx.x * TPB;
+  const int nt = min(TPB, p.T - t0);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  TableRow tr;
+  tr.load(p);
+  if (p.E <= kRouteWaves && p.d <= kRowChunks * 512) {
+    const int per = kRouteWaves / p.E, e = wave % p.E, g = wave / p.E;
+    if (g < per) {
+      u32x4 b[kRowChunks];
+#pragma unroll
+      for (int j = 0; j < kRowChunks; ++j) {
+        const int c = j * 512 + lane * 8;
+        b[j] = c < p.d ? *reinterpret_cast<const u32x4*>(p.wg + (int64_t)e * p.d + c)
+                       : u32x4{0, 0, 0, 0};
+      }
+      for (int t = g; t < nt; t += per) {
+        u32x4 a[kRowChunks];
+#pragma unroll
+        for (int j = 0; j < kRowChunks; ++j) {
+          const int c = j * 512 + lane * 8;
+          a[j] = c < p.d ? *reinterpret_cast<const u32x4*>(p.x + (int64_t)(t0 + t) * p.d + c)
+                         : u32x4{0, 0, 0, 0};
+        }
+        float acc = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kRowChunks; ++j) {
+          acc = dot2(a[j].x, b[j].x, acc);
+          acc = dot2(a[j].y, b[j].y, acc);
+          acc = dot2(a[j].z, b[j].z, acc);
+          acc = dot2(a[j].w, b[j].w, acc);
+        }
+        const float v = wave_sum_dpp(acc);
+        if (lane == 0) lg[t * p.E + e] = v;
+      }
+    }
   } else {
-    build_worklist(p, s_idx, s_prec, widths, wl, perm, pos);
+    gate_logits<1, 8>(p, t0, t0 + nt, lg);
+  }
+  tr.store(p, tags, widths);
+  __syncthreads();
+  for (int t = wave; t < nt; t += kRouteWaves)
+    decide_wave<FIRST>(p, t0 + t, lg + t * p.E, tags, o, nullptr, nullptr);
+}
+
+// Lanes of this wave with the same key as this lane (key >= 0, below 2^BITS).
+template <int BITS>
+__device__ inline uint64_t same_key(int key) {
+  uint64_t m = __ballot(key >= 0);
+#pragma unroll
+  for (int b = 0; b < BITS; ++b) {
+    const uint64_t on = __ballot(key >> b & 1);
+    m &= (key >> b & 1) ? on : ~on;
+  }
+  return m;
+}
+
+// Work list of any number of pairs: a stable counting sort by key = expert *
+// 2 + (low ? 1 : 0) in one block.  Wave w owns the pairs [w S, (w + 1) S);
+// it counts their keys (a pair's rank among equal keys of 64 pairs is the
+// number of lower lanes with that key, found with one ballot per key bit),
+// the counts are scanned over keys and waves, and the wave walks its pairs
+// again to place them.  Three block barriers whatever the number of pairs;
+// with a barrier between every 1024 pairs instead, 8192 tokens took 39 us.
+__global__ __launch_bounds__(kRouteThreads) void worklist_kernel(
+    RouteParams p, RouteOut o, WorkList* wl, int32_t* perm, int32_t* pos) {
+  constexpr int kKeyBits = 7;
+  static_assert(kMaxKeys == 1 << kKeyBits && kMaxKeys == 2 * 64, "two keys per lane of one wave");
+  __shared__ int widths[kMaxExperts], tags[kMaxExperts];
+  __shared__ int at[kRouteWaves][kMaxKeys];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int N = p.T * p.K;
+  const int S = ((N + kRouteThreads - 1) / kRouteThreads) * 64;
+  const int i0 = wave * S, i1 = min(i0 + S, N);
+  const uint64_t lower = (1ull << lane) - 1ull;
+  TableRow tr;
+  tr.load(p);
+  for (int v = tid; v < kRouteWaves * kMaxKeys; v += kRouteThreads) at[v / kMaxKeys][v % kMaxKeys] = 0;
+  tr.store(p, tags, widths);
+  __syncthreads();
+  auto key_of = [&](int i) {
+    int key = -1;
+    if (i < i1) {
+      const int pr = o.prec[i];
+      if (pr != PREC_SKIP) key = o.idx[i] * 2 + (pr == PREC_LOW);
+    }
+    return key;
+  };
+  for (int c = i0; c < i1; c += 64) {
+    const int key = key_of(c + lane);
+    const uint64_t m = same_key<kKeyBits>(key);
+    if (key >= 0 && (m & lower) == 0) atomicAdd(&at[wave][key], __popcll(m));
+  }
+  __syncthreads();
+  if (wave == 0) {
+    // lane l: keys 2 l and 2 l + 1
+    int cnt[2], run = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      cnt[h] = 0;
+#pragma unroll
+      for (int w = 0; w < kRouteWaves; ++w) cnt[h] += at[w][2 * lane + h];
+    }
+    const int mine = cnt[0] + cnt[1], mine_g = (cnt[0] > 0) + (cnt[1] > 0);
+    int off = mine, ng = mine_g, mx = max(cnt[0], cnt[1]);
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+      const int a = __shfl_up(off, s, 64), b = __shfl_up(ng, s, 64);
+      if (lane >= s) {
+        off += a;
+        ng += b;
+      }
+      mx = max(mx, __shfl_xor(mx, s, 64));
+    }
+    if (lane == 63) {
+      wl->n_groups = ng;
+      wl->max_count = mx;
+    }
+    off -= mine;
+    ng -= mine_g;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      run = off;
+      if (cnt[h] > 0) {
+        Group g;
+        g.expert = lane;
+        g.bits = copy_bits(widths[lane], h);
+        g.offset = off;
+        g.count = cnt[h];
+        wl->groups[ng++] = g;
+      }
+      off += cnt[h];
+      // first place of every wave's pairs of this key
+#pragma unroll
+      for (int w = 0; w < kRouteWaves; ++w) {
+        const int n = at[w][2 * lane + h];
+        at[w][2 * lane + h] = run;
+        run += n;
+      }
+    }
+  }
+  __syncthreads();
+  for (int c = i0; c < i1; c += 64) {
+    const int i = c + lane;
+    const int key = key_of(i);
+    const uint64_t m = same_key<kKeyBits>(key);
+    int first = 0;
+    if (key >= 0 && (m & lower) == 0) first = atomicAdd(&at[wave][key], __popcll(m));
+    first = __shfl(first, m ? __ffsll((unsigned long long)m) - 1 : 0, 64);
+    if (key >= 0) {
+      const int to = first + __popcll(m & lower);
+      perm[to] = i;
+      pos[i] = to;
+    } else if (i < i1) {
+      pos[i] = -1;
+    }
   }
 }
 
-// Prefill: many blocks route their tokens; a second kernel builds the list.
-__global__ __launch_bounds__(kPrefillThreads) void route_tokens_kernel(
-    RouteParams p, RouteOut o) {
-  __shared__ float lg[kPrefillTokPerBlock * kMaxExperts];
-  __shared__ int tags[kMaxExperts], widths[kMaxExperts];
-  const int t0 = blockIdx.x * kPrefillTokPerBlock;
-  const int t1 = min(t0 + kPrefillTokPerBlock, p.T);
-  stage_table(p, tags, widths);
-  gate_logits<kPrefillTokPerBlock, 8>(p, t0, t1, lg);
-  __syncthreads();
-  for (int t = t0 + (int)threadIdx.x; t < t1; t += blockDim.x)
-    decide_token(p, t, lg + (t - t0) * p.E, tags, o);
-}
-
-__global__ __launch_bounds__(kRouteThreads) void worklist_kernel(
-    RouteParams p, RouteOut o, WorkList* wl, int32_t* perm, int32_t* pos) {
-  __shared__ int tags[kMaxExperts], widths[kMaxExperts];
-  stage_table(p, tags, widths);
-  __syncthreads();
-  build_worklist(p, o.idx, o.prec, widths, wl, perm, pos);
+template <bool FIRST>
+hipError_t launch_route_tokens(const RouteParams& p, RouteOut o, WorkList* wl, int32_t* perm,
+                               int32_t* pos, hipStream_t s) {
+  // one token per block up to two blocks per compute unit
+  if (p.T <= 512) {
+    route_tokens_kernel<FIRST, 1><<<p.T, kRouteThreads, 0, s>>>(p, o);
+  } else {
+    route_tokens_kernel<FIRST, kMaxTokPerBlock>
+        <<<(p.T + kMaxTokPerBlock - 1) / kMaxTokPerBlock, kRouteThreads, 0, s>>>(p, o);
+  }
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  worklist_kernel<<<1, kRouteThreads, 0, s>>>(p, o, wl, perm, pos);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-bool route_decode_fuses_norm(int T, int d) { return fast_gate(T, d); }
+bool route_decode_fuses_norm(int T, int d) { return T <= kRouteSmallTokens && fast_gate(T, d); }
 
 hipError_t launch_route_decode(const RouteParams& p, RouteOut o, WorkList* wl,
                                int32_t* perm, int32_t* pos, hipStream_t s) {
   // the fused RMSNorm exists on the LDS-staged gate path only
-  if (p.h_res && !fast_gate(p.T, p.d)) return hipErrorInvalidValue;
+  if (p.h_res && !route_decode_fuses_norm(p.T, p.d)) return hipErrorInvalidValue;
+  if (p.T > kRouteSmallTokens) return launch_route_tokens<false>(p, o, wl, perm, pos, s);
   route_decode_kernel<<<1, kRouteThreads, 0, s>>>(p, o, wl, perm, pos);
   return hipGetLastError();
 }
 
 hipError_t launch_route_prefill(const RouteParams& p, RouteOut o, WorkList* wl,
                                 int32_t* perm, int32_t* pos, hipStream_t s) {
-  const int blocks = (p.T + kPrefillTokPerBlock - 1) / kPrefillTokPerBlock;
-  route_tokens_kernel<<<blocks, kPrefillThreads, 0, s>>>(p, o);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  worklist_kernel<<<1, kRouteThreads, 0, s>>>(p, o, wl, perm, pos);
-  return hipGetLastError();
+  return launch_route_tokens<true>(p, o, wl, perm, pos, s);
 }
 
 }  // namespace moe

@@ -250,6 +250,32 @@ def test_multi_token_steps_on_dot2_kernels(T):
                 residual=True)
 
 
+@pytest.mark.parametrize("d,E,K,T", [(320, 16, 2, 8), (320, 16, 2, 9), (128, 64, 8, 64),
+                                     (4160, 17, 3, 10), (64, 5, 5, 64), (576, 3, 1, 33)])
+def test_routers_of_larger_steps(d, E, K, T):
+    """Steps of up to 8 tokens are routed by one block, larger ones by a block
+    per token and a second kernel for the work list: the last step of the
+    one and the first of the other, more experts than a block has waves, rows
+    longer than the registers hold, up to 512 pairs, groups of every size."""
+    wl = _edge(f"edge_router_{d}_{E}_{K}_{T}", 39, d, 64, E, K, T,
+               [(C.TAG_FP16, C.TAG_INT4, C.TAG_MISS_INT2, C.TAG_MISS_INT4)[e % 4]
+                for e in range(E)], t1=0.3, t2=0.8)
+    rng = np.random.default_rng(300 + T)
+    _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, d)).astype(np.float16))
+
+
+@pytest.mark.parametrize("d,f,E,K,T", [(320, 448, 4, 2, 55), (320, 448, 4, 2, 56),
+                                       (2048, 2048, 2, 1, 27), (2048, 2048, 2, 1, 28)])
+def test_large_decode_batches(d, f, E, K, T):
+    """Either side of the step sizes from which decode takes the prefill
+    kernels (28 pairs per expert, 14 from d_model * d_ff = 2^22 on)."""
+    wl = _edge(f"edge_batch_{d}_{f}_{T}", 40, d, f, E, K, T,
+               [C.TAG_MISS_INT4, C.TAG_INT2, C.TAG_INT8, C.TAG_MISS_INT2][:E], t1=0.4, t2=0.9)
+    rng = np.random.default_rng(400 + T)
+    _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, d)).astype(np.float16))
+    _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, d)).astype(np.float16), residual=True)
+
+
 def test_reduction_chunks():
     """Matrix-core decode at 12 tokens over a long reduction: d = 4096 for
     the up-projection and a ragged f = 3520 for the down-projection (the
