@@ -188,6 +188,21 @@ bool decode_on_matrix_cores(int T, int K, int E) {
   return T > kDecodeDot2MaxTokens || T * K > E;
 }
 
+// Large decode batches take the prefill kernels, whose blocks hold 64 tokens
+// or more: the matrix-core decode kernels stream an expert copy once per 16
+// tokens of its group, so they fall behind when most groups have more.
+// Measured per step, decode / prefill kernels: Mixtral-shaped 4:3:1 with 48
+// and 64 tokens (12 and 16 per expert) 492 / 428 and 686 / 428 us, its int8
+// model 595 / 625 and 740 / 628; d 2048, f 4096 96 / 99 and 122 / 99; Phi-
+// shaped with 64 tokens (8 per expert) 374 / 382.  On small layers latency
+// counts and the decode kernels' smaller blocks hold on longer: d 1024, f
+// 2048 with 16 per expert 51 / 54, d 320, f 448 with 16, 24 and 32 24 / 27,
+// 26 / 27 and 30 / 27 us.
+bool decode_on_prefill_kernels(int T, int K, int E, int d, int f) {
+  const int64_t P = (int64_t)T * K;
+  return P >= 28 * (int64_t)E || (P >= 14 * (int64_t)E && (int64_t)d * f >= (1 << 22));
+}
+
 // The launch sequence of a decode step with the workspace `ws` (the layer's
 // arena, or the static scratch of the allocation-free entry point).
 // With prenorm, h_res is the residual stream on entry and x an output: the
@@ -214,14 +229,19 @@ moe_status decode_launch(moe_layer* l, const Workspace& ws, int32_t T, const voi
   HIP_TRY(launch_route_decode(rp, route_out(ws, idx, w, prec), ws.wl, ws.perm, ws.pos, s),
           "route kernel launch");
   HIP_TRY(mark(l, 1, s), "timing event");
-  if (decode_on_matrix_cores(T, K, l->desc.n_experts)) {
+  const int E = l->desc.n_experts;
+  if (decode_on_matrix_cores(T, K, E)) {
     // several tokens per expert copy: matrix-core kernels, per-pair down
     // rows and the fused combine (+ residual rmsnorm) of the prefill path
-    HIP_TRY(launch_decode_up_mfma(l->d_table, ws.wl, ws.perm, static_cast<const f16*>(x),
-                                  ws.h, d, f, K, mg, s), "up kernel launch");
+    const bool many = decode_on_prefill_kernels(T, K, E, d, f);
+    HIP_TRY(many ? launch_prefill_up(l->d_table, ws.wl, ws.perm, static_cast<const f16*>(x),
+                                     ws.h, T, d, f, E, K, mg, s)
+                 : launch_decode_up_mfma(l->d_table, ws.wl, ws.perm, static_cast<const f16*>(x),
+                                         ws.h, d, f, K, mg, s), "up kernel launch");
     HIP_TRY(mark(l, 2, s), "timing event");
-    HIP_TRY(launch_decode_down_mfma(l->d_table, ws.wl, ws.perm, ws.h, ws.eperm,
-                                    d, f, mg, s), "down kernel launch");
+    HIP_TRY(many ? launch_prefill_down(l->d_table, ws.wl, ws.h, ws.eperm, T, d, f, E, K, mg, s)
+                 : launch_decode_down_mfma(l->d_table, ws.wl, ws.perm, ws.h, ws.eperm,
+                                           d, f, mg, s), "down kernel launch");
     HIP_TRY(launch_combine_prefill(ws.eperm, ws.pos, ws.w, ws.prec, T, d, K, y, h_res,
                                    static_cast<f16*>(x_next), l->desc.rms_eps, s),
             "combine kernel launch");
