@@ -119,6 +119,24 @@ def test_quantize_bit_exact(bits):
         assert np.array_equal(codes, O.pack_codes(q, bits)), w.shape
 
 
+@pytest.mark.parametrize("bits", [8, 4, 2])
+@pytest.mark.parametrize("rows,cols", [(1, 32), (5, 416), (255, 32), (16, 512), (257, 32), (33, 1056)])
+def test_quantize_any_bits_bit_exact(rows, cols, bits):
+    """Group counts around the quantiser's wave (64 groups) and block (256),
+    every finite fp16 bit pattern equally likely (subnormals, groups of very
+    different magnitudes), and groups of exact half-way quotients."""
+    rng = np.random.default_rng(1000 * rows + cols + bits)
+    w = rng.integers(0, 65536, (rows, cols)).astype(np.uint16).view(np.float16)
+    w = np.where(np.isfinite(w), w, np.float16(0)).astype(np.float16)
+    half = rng.integers(-2 * ((1 << (bits - 1)) - 1), 2 * (1 << (bits - 1)) - 1, (rows, cols))
+    ties = (half * 0.5 * 2.0 ** rng.integers(-12, 4, (rows, 1))).astype(np.float16)
+    for v in (w, ties, (w.astype(np.float32) * 2.0 ** -20).astype(np.float16)):
+        codes, scales = _quant_device(v, bits)
+        q, s = O.quantize(v, bits)
+        assert np.array_equal(scales.view(np.uint16), s.view(np.uint16))
+        assert np.array_equal(codes, O.pack_codes(q, bits))
+
+
 def test_export_packed_matches_quantizer():
     wl = C.TINY
     tags = C.layer_tags(wl, 0)
