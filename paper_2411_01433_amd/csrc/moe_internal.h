@@ -82,6 +82,29 @@ __device__ inline float wave_sum_dpp(float v) {
   return __builtin_bit_cast(float, (uint32_t)r32[0]) + __builtin_bit_cast(float, (uint32_t)r32[1]);
 }
 
+// Max of the keys of a wave's lanes, in every lane (as wave_sum_dpp).
+template <int CTRL>
+__device__ inline uint32_t dpp_max(uint32_t v) {
+  const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+  return o > v ? o : v;
+}
+__device__ inline uint32_t wave_max_u32(uint32_t v) {
+  v = dpp_max<0xB1>(v);   // quad_perm [1,0,3,2]
+  v = dpp_max<0x4E>(v);   // quad_perm [2,3,0,1]
+  v = dpp_max<0x141>(v);  // row_half_mirror
+  v = dpp_max<0x140>(v);  // row_mirror
+  const auto r16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = (uint32_t)r16[0] > (uint32_t)r16[1] ? (uint32_t)r16[0] : (uint32_t)r16[1];
+  const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return (uint32_t)r32[0] > (uint32_t)r32[1] ? (uint32_t)r32[0] : (uint32_t)r32[1];
+}
+
+// Order-preserving key of a float (larger float, larger key; -inf above 0).
+__device__ inline uint32_t float_key(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
 // Residual RMSNorm of the residual glue, x = fp16(v / sqrt(mean(v^2) + eps)),
 // for rows t0 .. t0 + nb - 1 (nb <= NB) of h (fp32 [*, d], d a multiple of 64
 // and at most 4096 * PIECES), by one block of kNormThreads threads.  Thread i

@@ -183,15 +183,10 @@ __device__ void gate_fast(const RouteParams& p, f16* xs, float* lg) {
   }
 }
 
-// Order-preserving key of a float (larger float, larger key).
-__device__ inline uint32_t float_key(float v) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, v);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 // top-k, softmax over the selected logits and the Eq. 2 rule for token t by
-// one wave: lanes are experts; slot k is the wave maximum of (logit, -index)
-// over the experts not yet taken, so exact ties keep the lower index.  lrow:
+// one wave: lanes are experts; slot k is the lowest lane with the wave maximum
+// of the logits' keys over the experts not yet taken, so exact ties keep the
+// lower index.  lrow:
 // the token's E logits in LDS; s_idx / s_prec: the pairs in LDS, or null.
 // A NaN logit: a decode step's router (FIRST = false) takes it as larger than
 // any number (smaller with the sign bit), a prefill's as one that is only
@@ -207,21 +202,18 @@ __device__ void decide_wave(const RouteParams& p, int t, const float* lrow, cons
 #pragma unroll
   for (int k = 0; k < kMaxTopK; ++k) {
     if (k >= p.K) break;
-    uint64_t key = ((uint64_t)float_key(v) << 32) | (uint32_t)(63 - lane);
+    uint32_t key = float_key(v);
     if (FIRST) {
       const int first = __ffsll((unsigned long long)~taken) - 1;
-      if (v != v) key = ((uint64_t)(lane == first ? 0xFFFFFFFFu : 0u) << 32) | (uint32_t)(63 - lane);
+      if (v != v) key = lane == first ? 0xFFFFFFFFu : 1u;
       if (taken >> lane & 1) key = 0;
     }
-    if (lane >= p.E) key = 0;  // never selected (E >= K experts remain)
-#pragma unroll
-    for (int o_ = 32; o_ > 0; o_ >>= 1) {
-      const uint64_t other = __shfl_xor(key, o_, 64);
-      key = other > key ? other : key;
-    }
-    const int e = 63 - (int)(key & 63u);
+    if (lane >= p.E) key = 0;  // (ties go to lower lanes, and E >= K)
+    const uint32_t top = wave_max_u32(key);
+    const int e = __ffsll((unsigned long long)__ballot(key == top)) - 1;
     sel[k] = e;
-    ls[k] = __shfl(v, e, 64);
+    ls[k] = __builtin_bit_cast(
+        float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), __builtin_amdgcn_readfirstlane(e)));
     if (FIRST) taken |= 1ull << e;
     else if (lane == e) v = -__builtin_inff();
   }

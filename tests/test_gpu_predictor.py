@@ -120,6 +120,28 @@ def test_predictor_ragged_and_wide():
     _check(x, gates, cached, 8, _run(256, 64, 8, x, gates, cached))
 
 
+@pytest.mark.parametrize("T,p", [(1, 1), (2, 4), (3, 3)])
+@pytest.mark.parametrize("E,K", [(64, 8), (16, 16 // 2), (1, 1)])
+def test_predictor_ties_and_rounds(T, p, E, K):
+    """Exact ties (every second gate row repeats the one before it) keep the
+    lower index, on both sides of the count of (token, layer) pairs up to
+    which a wave takes each."""
+    rng = np.random.default_rng(9)
+    x = rng.standard_normal((T, 128)).astype(np.float16)
+    gates = []
+    for _ in range(p):
+        g = (rng.standard_normal((E, 128)) * 0.3).astype(np.float16)
+        g[1::2] = g[:(E // 2) * 2:2]
+        gates.append(g)
+    cached = _masks(rng, E, p)
+    idx = _run(128, E, K, x, gates, cached)[0]
+    for t in range(T):
+        for j in range(p):
+            lg = x[t].astype(np.float64) @ gates[j].astype(np.float64).T
+            want = np.lexsort((np.arange(E), -lg))[:K]
+            np.testing.assert_array_equal(idx[t, j], want)
+
+
 def test_predictor_prefill_sized():
     """512 tokens (the prefill batch), p = 2."""
     wl = C.MIXTRAL_PREFILL
