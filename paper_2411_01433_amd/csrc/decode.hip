@@ -26,8 +26,9 @@
 // row tile, so every selected expert copy is streamed from HBM once per step
 // whatever the number of tokens routed to it.  Down-projection blocks each
 // take a row tile of d_model and loop over all work groups, accumulating
-// w[p] * e into the token's output row in LDS in work-list order, so the
-// combine needs no extra pass and the sum order is fixed (deterministic).
+// w[p] * e into the token's output row in LDS in work-list order (per wave
+// where a wave takes groups alone, then the waves in order), so the combine
+// needs no extra pass and the sum order is fixed (deterministic).
 #include "moe_internal.h"
 
 namespace moe {
@@ -44,6 +45,7 @@ constexpr int kWaves = kThreads / 64;
 // with 4-row down tiles: 109 us).
 template <int NTMAX> struct UpRows { static constexpr int value = NTMAX <= 2 ? 2 : 4; };
 template <int NTMAX> struct DownRows { static constexpr int value = NTMAX <= 2 ? 4 : 8; };
+constexpr int kOwnGroupMaxF = 8192;  // longest rows whose groups a wave takes alone
 
 // Scalar-argument casts on purpose: clang's __builtin_bit_cast applied
 // directly to a vector component expression (v.y) reads component 0.
@@ -51,12 +53,6 @@ __device__ inline f16x2 as_h2(uint32_t v) { return __builtin_bit_cast(f16x2, v);
 
 __device__ inline float dot2(uint32_t a, uint32_t b, float acc) {
   return __builtin_amdgcn_fdot2(as_h2(a), as_h2(b), acc, false);
-}
-
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
 }
 
 // low half of a | low half of b  /  high half of a | high half of b
@@ -239,9 +235,11 @@ template <> struct Piece<2> {
   }
 };
 
-// Partial dot products of this wave's chunks for ROWS rows of NM matrices
-// (matrix ids mats) against NT activation rows act_rows[t] (length ld).
-template <int BITS, int NT, int NM, int ROWS>
+// Partial dot products of this wave's chunks (every STRIDE-th one: kWaves
+// where the waves split the reduction, 1 where a wave takes all of it) for
+// ROWS rows of NM matrices (matrix ids mats) against NT activation rows
+// act_rows[t] (length ld).
+template <int BITS, int NT, int NM, int ROWS, int STRIDE = kWaves>
 __device__ inline void tile_dots(const ExpertEntry& ex, const int (&mats)[NM],
                                  int64_t row0, int64_t ld,
                                  const f16* const (&act_rows)[NT],
@@ -250,7 +248,7 @@ __device__ inline void tile_dots(const ExpertEntry& ex, const int (&mats)[NM],
   constexpr int kChunk = 64 * kEpl;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n_chunks = (int)((ld + kChunk - 1) / kChunk);
-  for (int c = wave; c < n_chunks; c += kWaves) {
+  for (int c = STRIDE == 1 ? 0 : wave; c < n_chunks; c += STRIDE) {
     const int64_t col = (int64_t)c * kChunk + lane * kEpl;
     if (col >= ld) continue;  // ragged last chunk (ld is a multiple of 64)
     uint32_t a[NT][kEpl / 2];
@@ -463,7 +461,57 @@ __device__ void down_group(const ExpertEntry& ex, const int32_t* pairs, int coun
   }
 }
 
+// The same for one wave and one group, the whole reduction in this wave.
+template <int BITS, int NT, int ROWS>
+__device__ void down_tile_wave(const ExpertEntry& ex, const int32_t* pairs, int n,
+                               const f16* h, const float* gate_w, int f, int K,
+                               int64_t row0, float* yacc) {
+  const f16* rows[NT];
+  float gw[NT];
+  int tok[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int p = pairs[t < n ? t : 0];
+    rows[t] = h + (int64_t)p * f;
+    gw[t] = gate_w[p];
+    tok[t] = p / K;
+  }
+  float acc[1][ROWS][NT];
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[0][i][t] = 0.0f;
+  const int mats[1] = {2};
+  tile_dots<BITS, NT, 1, ROWS, 1>(ex, mats, row0, f, rows, acc);
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const float s = wave_sum_dpp(acc[0][i][t]);
+      if ((threadIdx.x & 63) == 0 && t < n) yacc[tok[t] * ROWS + i] += gw[t] * s;
+    }
+}
+
+template <int BITS, int ROWS>
+__device__ void down_group_wave(const ExpertEntry& ex, const int32_t* pairs, int count,
+                                const f16* h, const float* gate_w, int f, int K,
+                                int64_t row0, float* yacc) {
+  for (int j0 = 0; j0 < count; j0 += 2) {
+    const int n = min(2, count - j0);
+    if (n == 1) down_tile_wave<BITS, 1, ROWS>(ex, pairs + j0, n, h, gate_w, f, K, row0, yacc);
+    else down_tile_wave<BITS, 2, ROWS>(ex, pairs + j0, n, h, gate_w, f, K, row0, yacc);
+  }
+}
+
 // y[t, rows] (or h_res[t, rows] += ...) for one row tile, all work groups.
+// The waves split each group's reduction, or, with at least as many groups as
+// waves and rows short enough (f <= 8192), every wave takes groups of its
+// own: a split group costs the block two barriers and a chain of loads
+// (group, expert, pairs, activations) that nothing overlaps, which on small
+// layers is all there is.  Per step, split / own groups: d 256, f 512, 4
+// tokens 20.5 / 15.5 us, d 1024, f 2048, 4 tokens 33.4 / 29.0; Phi-shaped
+// down-projection, 4 tokens (f 6400) 47.6 / 44.7; Mixtral-shaped (f 14336)
+// 79 / 84 us, its groups' widths differing too much to balance over a block.
 template <int NTMAX>
 __global__ __launch_bounds__(kThreads) void decode_down_kernel(
     const ExpertEntry* __restrict__ table, const WorkList* __restrict__ wl,
@@ -472,25 +520,44 @@ __global__ __launch_bounds__(kThreads) void decode_down_kernel(
     int T, int d, int f, int K) {
   constexpr int R = DownRows<NTMAX>::value;
   __shared__ float red[(kWaves + 1) * R * NTMAX];
-  __shared__ float yacc[kDecodeMaxTokens * R];
+  __shared__ float yacc[kWaves * kDecodeDot2MaxTokens * R];
   const int64_t row0 = (int64_t)blockIdx.x * R;
-  for (int v = threadIdx.x; v < T * R; v += kThreads) yacc[v] = 0.0f;
-  __syncthreads();
   const int n_groups = wl->n_groups;
-  for (int gi = 0; gi < n_groups; ++gi) {
-    const Group g = wl->groups[gi];
-    const ExpertEntry ex = table[g.expert];
-    const int32_t* pairs = perm + g.offset;
-    if (g.bits == 16) down_group<16, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
-    else if (g.bits == 8) down_group<8, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
-    else if (g.bits == 4) down_group<4, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
-    else down_group<2, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
+  const bool split = NTMAX == 1 || n_groups < kWaves || f > kOwnGroupMaxF;
+  const int parts = split ? 1 : kWaves;  // partial sums of y in LDS
+  for (int v = threadIdx.x; v < parts * T * R; v += kThreads) yacc[v] = 0.0f;
+  __syncthreads();
+  if (split) {
+    for (int gi = 0; gi < n_groups; ++gi) {
+      const Group g = wl->groups[gi];
+      const ExpertEntry ex = table[g.expert];
+      const int32_t* pairs = perm + g.offset;
+      if (g.bits == 16) down_group<16, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
+      else if (g.bits == 8) down_group<8, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
+      else if (g.bits == 4) down_group<4, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
+      else down_group<2, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
+    }
+  } else if constexpr (NTMAX > 1) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float* mine = yacc + wave * T * R;
+    for (int gi = wave; gi < n_groups; gi += kWaves) {
+      const Group g = wl->groups[gi];
+      const ExpertEntry ex = table[g.expert];
+      const int32_t* pairs = perm + g.offset;
+      if (g.bits == 16) down_group_wave<16, R>(ex, pairs, g.count, h, gate_w, f, K, row0, mine);
+      else if (g.bits == 8) down_group_wave<8, R>(ex, pairs, g.count, h, gate_w, f, K, row0, mine);
+      else if (g.bits == 4) down_group_wave<4, R>(ex, pairs, g.count, h, gate_w, f, K, row0, mine);
+      else down_group_wave<2, R>(ex, pairs, g.count, h, gate_w, f, K, row0, mine);
+    }
+    __syncthreads();
   }
   for (int v = threadIdx.x; v < T * R; v += kThreads) {
     const int t = v / R, i = v - t * R;
     const int64_t o = (int64_t)t * d + row0 + i;
-    if (h_res) h_res[o] += yacc[v];
-    else y[o] = yacc[v];
+    float s = yacc[v];
+    for (int w = 1; w < parts; ++w) s += yacc[w * T * R + v];
+    if (h_res) h_res[o] += s;
+    else y[o] = s;
   }
 }
 

@@ -294,6 +294,17 @@ def test_large_decode_batches(d, f, E, K, T):
     _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, d)).astype(np.float16), residual=True)
 
 
+@pytest.mark.parametrize("f", [64, 8192, 8256])
+@pytest.mark.parametrize("T", [2, 4])
+def test_dot2_down_projection_group_split(f, T):
+    """Either side of the row length from which the down-projection's waves
+    split each group instead of taking groups of their own."""
+    wl = _edge(f"edge_own_groups_{f}_{T}", 41, 64, f, 16, 4, T,
+               [C.TAG_FP16, C.TAG_INT4, C.TAG_INT2, C.TAG_INT8] * 4)
+    rng = np.random.default_rng(500 + T)
+    _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, 64)).astype(np.float16), residual=True)
+
+
 def test_reduction_chunks():
     """Matrix-core decode at 12 tokens over a long reduction: d = 4096 for
     the up-projection and a ragged f = 3520 for the down-projection (the
