@@ -118,6 +118,10 @@ def lib() -> ctypes.CDLL:
     L.moe_store_destroy.argtypes = [vp]
     L.moe_layer_bind_expert.argtypes = [vp, i32, i32, ctypes.POINTER(vp), ctypes.POINTER(vp),
                                         ctypes.POINTER(vp), i32, vp]
+    L.moe_predictor_init.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(vp), vp,
+                                     ctypes.POINTER(vp)]
+    L.moe_predict.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp, vp]
+    L.moe_predictor_destroy.argtypes = [vp]
     L.moe_rmsnorm.argtypes = [vp, vp, i32, i32, ctypes.c_float, vp]
     L.moe_last_error.restype = ctypes.c_char_p
     for name in EXPORTED:
@@ -132,11 +136,41 @@ def _check(status: int):
         raise MoeError(status, lib().moe_last_error().decode())
 
 
+# The calls a program makes per token marshal in a few microseconds, which a
+# short step (the predictor: 6 us on the GPU) would otherwise wait for: torch
+# is looked up once, the current stream is read without making a Stream, and
+# an argument that is what it should be is checked by plain comparisons and
+# passed as its address.
+_torch = None
+
+
+def _th():
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _stream(stream):
-    import torch
+    """The hipStream_t (an int) of a torch stream, an int or None (current)."""
     if stream is None:
+        torch = _th()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _addr(t, dtype, shape, name):
+    """Address of a tensor argument (None: NULL), checked as by _ptr."""
+    if t is None:
+        return None
+    if (isinstance(t, _th().Tensor) and t.is_cuda and t.dtype is dtype and t.shape == shape
+            and t.is_contiguous()):
+        return t.data_ptr()
+    return _ptr(t, dtype, shape, name).value
 
 
 def _ptr(t, dtype, shape=None, name="tensor"):
@@ -156,20 +190,20 @@ def _ptr(t, dtype, shape=None, name="tensor"):
 
 def quantize(w, bits: int, codes, scales, stream=None):
     """Quantise an fp16 device matrix w [rows, cols] into codes / scales."""
-    import torch
+    torch = _th()
     rows, cols = w.shape
     _check(lib().moe_quantize(
-        _ptr(w, torch.float16, None, "w"), rows, cols, bits,
-        _ptr(codes, torch.uint8, (rows, cols * bits // 8), "codes"),
-        _ptr(scales, torch.float16, (rows, cols // 32), "scales"), _stream(stream)))
+        _addr(w, torch.float16, (rows, cols), "w"), rows, cols, bits,
+        _addr(codes, torch.uint8, (rows, cols * bits // 8), "codes"),
+        _addr(scales, torch.float16, (rows, cols // 32), "scales"), _stream(stream)))
 
 
 def rmsnorm(h, x, eps: float = 1e-5, stream=None):
     """x = fp16(rmsnorm(h)) row by row (h fp32 [T, d], x fp16 [T, d])."""
-    import torch
+    torch = _th()
     T, d = h.shape
-    _check(lib().moe_rmsnorm(_ptr(h, torch.float32, None, "h"),
-                             _ptr(x, torch.float16, (T, d), "x"), T, d, eps, _stream(stream)))
+    _check(lib().moe_rmsnorm(_addr(h, torch.float32, (T, d), "h"),
+                             _addr(x, torch.float16, (T, d), "x"), T, d, eps, _stream(stream)))
 
 
 class MoeLayer:
@@ -208,24 +242,24 @@ class MoeLayer:
         _check(lib().moe_set_expert_precision(self._h, expert, tag, _stream(stream)))
 
     def _outs(self, T, topk_idx, topk_w, prec_used):
-        import torch
-        return (_ptr(topk_idx, torch.int32, (T, self.K), "topk_idx"),
-                _ptr(topk_w, torch.float32, (T, self.K), "topk_w"),
-                _ptr(prec_used, torch.int8, (T, self.K), "prec_used"))
+        torch, shape = _th(), (T, self.K)
+        return (_addr(topk_idx, torch.int32, shape, "topk_idx"),
+                _addr(topk_w, torch.float32, shape, "topk_w"),
+                _addr(prec_used, torch.int8, shape, "prec_used"))
 
     def _step(self, fn, x, y, topk_idx, topk_w, prec_used, stream):
-        import torch
+        torch = _th()
         T = x.shape[0]
-        _check(fn(self._h, T, _ptr(x, torch.float16, (T, self.d), "x"),
-                  _ptr(y, torch.float32, (T, self.d), "y"),
+        _check(fn(self._h, T, _addr(x, torch.float16, (T, self.d), "x"),
+                  _addr(y, torch.float32, (T, self.d), "y"),
                   *self._outs(T, topk_idx, topk_w, prec_used), _stream(stream)))
 
     def _step_res(self, fn, x, h, x_next, topk_idx, topk_w, prec_used, stream):
-        import torch
+        torch = _th()
         T = x.shape[0]
-        _check(fn(self._h, T, _ptr(x, torch.float16, (T, self.d), "x"),
-                  _ptr(h, torch.float32, (T, self.d), "h"),
-                  _ptr(x_next, torch.float16, (T, self.d), "x_next"),
+        _check(fn(self._h, T, _addr(x, torch.float16, (T, self.d), "x"),
+                  _addr(h, torch.float32, (T, self.d), "h"),
+                  _addr(x_next, torch.float16, (T, self.d), "x_next"),
                   *self._outs(T, topk_idx, topk_w, prec_used), _stream(stream)))
 
     def decode_step(self, x, y, topk_idx=None, topk_w=None, prec_used=None, stream=None):
@@ -248,11 +282,11 @@ class MoeLayer:
                             stream=None):
         """moe_decode_step_prenorm: x = fp16(rmsnorm(h)) formed by the step, then
         h += MoE(x) (h is the residual stream, x an output)."""
-        import torch
+        torch = _th()
         T = h.shape[0]
         _check(lib().moe_decode_step_prenorm(
-            self._h, T, _ptr(h, torch.float32, (T, self.d), "h"),
-            _ptr(x, torch.float16, (T, self.d), "x"),
+            self._h, T, _addr(h, torch.float32, (T, self.d), "h"),
+            _addr(x, torch.float16, (T, self.d), "x"),
             *self._outs(T, topk_idx, topk_w, prec_used), _stream(stream)))
 
     def prefill_residual(self, x, h, x_next, topk_idx=None, topk_w=None,
@@ -344,15 +378,15 @@ class MoePredictor:
     def predict(self, x, cached, pred_idx, first_miss, preload, pred_w=None, stream=None):
         """x [T, d] fp16; cached int64 [p] (bit masks); pred_idx int32 [T, p, K];
         first_miss int32 [1]; preload int64 [1]; pred_w fp32 [T, p, K] or None."""
-        import torch
+        torch = _th()
         T = x.shape[0]
         _check(lib().moe_predict(
-            self._h, T, _ptr(x, torch.float16, (T, self.d), "x"),
-            _ptr(cached, torch.int64, (self.p,), "cached"),
-            _ptr(pred_idx, torch.int32, (T, self.p, self.K), "pred_idx"),
-            _ptr(pred_w, torch.float32, (T, self.p, self.K), "pred_w"),
-            _ptr(first_miss, torch.int32, (1,), "first_miss"),
-            _ptr(preload, torch.int64, (1,), "preload"), _stream(stream)))
+            self._h, T, _addr(x, torch.float16, (T, self.d), "x"),
+            _addr(cached, torch.int64, (self.p,), "cached"),
+            _addr(pred_idx, torch.int32, (T, self.p, self.K), "pred_idx"),
+            _addr(pred_w, torch.float32, (T, self.p, self.K), "pred_w"),
+            _addr(first_miss, torch.int32, (1,), "first_miss"),
+            _addr(preload, torch.int64, (1,), "preload"), _stream(stream)))
 
     def destroy(self):
         if self._h is not None and self._h.value:

@@ -179,3 +179,12 @@ def test_store_and_bind_reject_bad_args():
     assert L.moe_store_destroy(None) == B.MOE_EINVAL
     assert L.moe_store_sizes(bogus, None, None, None) == B.MOE_ESTATE
     assert L.moe_layer_bind_expert(bogus, 0, 0, None, None, None, 0, None) == B.MOE_ESTATE
+
+
+def test_binding_refuses_host_tensors_and_other_objects():
+    torch = pytest.importorskip("torch")
+    from paper_2411_01433_amd import binding as B
+    for t in (torch.zeros((2, 64), dtype=torch.float16), [0.0], 7):
+        with pytest.raises(ValueError, match="device tensor"):
+            B._addr(t, torch.float16, (2, 64), "x")
+    assert B._addr(None, torch.float16, (2, 64), "x") is None
