@@ -18,12 +18,16 @@
 // what feeds them: the LDS port, and the cycles in which a wave issues loads
 // instead of products.  With few tokens the HBM stream of the weights does.
 // A block is 4 waves, one per SIMD and with the whole unit's registers and
-// LDS, and owns 64 RT weight rows (in the up-projection half of them W1, the
-// other half the same rows of W3) x up to 256 tokens; a wave owns 32 RT rows
-// x half of the tokens as v_mfma_f32_32x32x16_f16 tiles (weights are the A
-// operand: lane l holds A[l%32][8(l/32)+i], B[8(l/32)+i][l%32] and
-// C[8(i/4)+4(l/32)+i%4][l%32]).  At RT = 4 and 256 tokens a step of 16
-// columns reads 8 fragments from LDS for 16 products.
+// LDS, and owns 128 RT weight rows (in the up-projection half of them W1, the
+// other half the same rows of W3) x up to 256 tokens as
+// v_mfma_f32_32x32x16_f16 tiles (weights are the A operand: lane l holds
+// A[l%32][8(l/32)+i], B[8(l/32)+i][l%32] and C[8(i/4)+4(l/32)+i%4][l%32]).  A
+// wave owns RT tiles of 32 rows and all of the tokens, MT tiles of 32: each
+// code is dequantised by one wave, and a block computes no more than 31
+// tokens too many.  With the waves 2 x 2 over rows and tokens instead, codes
+// were dequantised twice and tokens came in steps of 64: 512 tokens 604 ->
+// 539 us per layer, 64 tokens 432 -> 371, 8192 tokens 5278 -> 5097 (all fp16:
+// no change, although a step now reads 10 fragments for 16 products, not 8).
 //
 // Staging.  Both operands go to LDS by direct global-to-LDS loads of 16
 // bytes per lane: activations (gathered through the permutation) in stages
@@ -61,17 +65,17 @@
 // Measured (one layer, up / down-projection, us; before: 16x16x32 products,
 // 16 or 32 weight rows per wave, 160 tokens per pass, weights in register
 // rings, activations through LDS):
-//   Mixtral shape, 4:3:1 fp16:int4:int2, 8192 tokens 5863 / 3407 -> 3529 /
-//   1905 (1.09 and 1.01 PFLOP/s; a large fp16 library GEMM reaches 1.48),
-//   512 tokens 455 / 292 -> 443 / 267; half fp16 half int4, 64 tokens 369 /
-//   184 -> 326 / 186; Phi shape, 1024 tokens 441 / 257 -> 410 / 194; d 320,
-//   f 448, 6 experts, 1024 tokens 43 / 33 -> 14 / 17.
+//   Mixtral shape, 4:3:1 fp16:int4:int2, 8192 tokens 5863 / 3407 -> 3396 /
+//   1795 (1.13 and 1.07 PFLOP/s; a large fp16 library GEMM reaches 1.48),
+//   512 tokens 455 / 292 -> 380 / 226; half fp16 half int4, 64 tokens 369 /
+//   184 -> 240 / 119 (5.0 TB/s); Phi shape, 1337 tokens 752 / 391 -> 432 /
+//   193; d 320, f 448, 6 experts, 1337 tokens 55 / 42 -> 14 / 16.
 // On the way, at 8192 tokens and fp16 only (up): 8 waves of 64 rows x 128
 // tokens 3.85 ms; 4 waves 3.70; fragment reads two quarters early and the
 // short SwiGLU 3.60; remainders last 3.55; three activation stages instead
-// of two 3.38.
+// of two 3.38.  Blocks in the order of copy widths, or fp16 and narrow ones
+// alternating, moved nothing (512 tokens 546 - 552 us).
 #include <cstddef>
-#include <type_traits>
 
 #include "moe_internal.h"
 
@@ -81,13 +85,13 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kStageK = 64;                       // columns per stage, 4 steps of 16
-constexpr int kTileTok = 256;                     // tokens per block (MT = 4)
+constexpr int kTileTok = 256;                     // tokens per block (MT = 8)
 constexpr int kScaleStages = 4;                   // stages per unit of scales
 constexpr uint32_t kLdsBytes = 160 * 1024;
 constexpr int kMaxSlots = 8;
 
-// Geometry of a block of 64 RT weight rows (a wave: RT tiles of 32) and 64
-// MT tokens (a wave: MT tiles of 32), and its LDS rings: kASlots stages of
+// Geometry of a block of 128 RT weight rows (a wave: RT tiles of 32) and 32
+// MT tokens (every wave: all MT tiles of 32), and its LDS rings: kASlots stages of
 // activations (128 bytes of each row), kWSlots units of weights (fp16: 128
 // bytes of each row = one stage, codes: 64 bytes = kUnit stages) and of
 // scales (16 bytes of each row).  All rings are as deep as the LDS allows;
@@ -95,11 +99,11 @@ constexpr int kMaxSlots = 8;
 // go first in a stage and arrive within it, while the activations have two
 // stages.
 template <int BITS, int RT, int MT> struct Ring {
-  static constexpr int kRows = 64 * RT;
+  static constexpr int kRows = 128 * RT;
   static constexpr int kSubRows = kRows / 2;       // rows of each of the two sub-blocks
   static constexpr int kRowBytes = BITS == 16 ? 128 : 64;
   static constexpr int kUnit = BITS == 16 ? 1 : 8 / BITS;
-  static constexpr uint32_t kASlot = MT * 64 * 128;
+  static constexpr uint32_t kASlot = MT * 32 * 128;
   static constexpr uint32_t kWSlot = kRows * kRowBytes;
   static constexpr uint32_t kSSlot = BITS == 16 ? 0 : kRows * 16;
   static constexpr int kFit = (int)(kLdsBytes / (kASlot + kWSlot + kSSlot));
@@ -110,9 +114,9 @@ template <int BITS, int RT, int MT> struct Ring {
   static_assert(kSBase + kWSlots * kSSlot <= kLdsBytes, "LDS");
   // loads per wave: activations per stage, weights and scales per unit, and
   // the fewest of those that a stage issues
-  static constexpr int kALoads = 2 * MT;
-  static constexpr int kWUnitLoads = RT * kRowBytes / 64;
-  static constexpr int kSUnitLoads = BITS == 16 ? 0 : RT;
+  static constexpr int kALoads = MT;
+  static constexpr int kWUnitLoads = RT * kRowBytes / 32;
+  static constexpr int kSUnitLoads = BITS == 16 ? 0 : 2 * RT;
   static constexpr int kWLoads = kWUnitLoads / kUnit, kSLoads = kSUnitLoads / kScaleStages;
   static constexpr int kLoads = kWLoads + kSLoads + kALoads;
   // loads that may be in flight when a stage ends: those of the stages
@@ -226,9 +230,9 @@ struct Sub {
   int rows0, rows1;  // rows left in the matrix from the sub-block's first
 };
 
-// acc[i][t] (C tile: 32 weight rows x 32 tokens) of the wave's weight tile
-// i (tiles 0, 1: sub-block 0; 2, 3: sub-block 1) and token tile t, over all
-// of the ld columns.  act: row 0 of the block's activations (gather: x,
+// acc[i][t] (C tile: 32 weight rows x 32 tokens) of the wave's weight tile i
+// and token tile t, over all of the ld columns; RT = 2: tile i is 32 rows of
+// sub-block i, RT = 1: 16 rows of either.  act: row 0 of the block's activations (gather: x,
 // whose rows are perm[...] / K); n tokens.
 template <int BITS, int RT, int MT, bool GATHER>
 __device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act,
@@ -275,8 +279,8 @@ __device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act
   // load p of scale unit v: dword 4 v + l % 4 (two groups each) of rows
   // 64 p + 16 wave + l / 4
   auto load_s = [&](int v, int p, uint32_t slot) {
-    const bool second = p >= RT / 2;
-    const int r = min(64 * (p % (RT / 2)) + 16 * wave + (l >> 2), (second ? sub.rows1 : sub.rows0) - 1);
+    const bool second = p >= RT;
+    const int r = min(64 * (p % RT) + 16 * wave + (l >> 2), (second ? sub.rows1 : sub.rows0) - 1);
     const int dw = min(4 * v + (l & 3), ld / 64 - 1);
     lds_load4(lds0 + R::kSBase + slot * R::kSSlot + p * 1024 + wave * 256, second ? sub.s1 : sub.s0,
               (uint32_t)r * (uint32_t)(ld / 16) + 4 * dw);
@@ -304,13 +308,15 @@ __device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act
 
   const int half = l >> 5;
   const int sw = (l >> 1) & 7, sw64 = (l >> 2) & 3;              // chunk swizzles of this lane's rows
-  const uint32_t arow = (uint32_t)((wave & 1) * (32 * MT) + (l & 31)) * 128;   // token tile 0
-  const uint32_t wrow = (uint32_t)((wave >> 1) * (16 * RT) + (l & 31));        // weight tile 0
+  const uint32_t arow = (uint32_t)(l & 31) * 128;                // token tile 0
+  // weight tile 0: RT = 2, 32 rows of sub-block 0 (tile 1: the same rows of
+  // sub-block 1); RT = 1, 16 rows of each sub-block
+  const uint32_t wrow = RT == 2 ? (uint32_t)(wave * 32 + (l & 31))
+                                : (uint32_t)(wave * 16 + (l & 15) + (l & 16 ? R::kSubRows : 0));
   uint32_t cat[4];  // position of the lane's chunk of each step
 #pragma unroll
   for (int s = 0; s < 4; ++s) cat[s] = 16 * ((4 * half + s) ^ sw);
-  // row of weight tile i relative to tile 0
-  auto tile_row = [](int i) { return (uint32_t)(i % (RT / 2) * 32 + i / (RT / 2) * R::kSubRows); };
+  auto tile_row = [](int i) { return (uint32_t)(i * R::kSubRows); };  // tile i, relative to tile 0
 
   f16x8 a[2][MT], b[2][RT];
   u32x4 q[RT][Codes<BITS>::kRaw];
@@ -353,17 +359,15 @@ __device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act
                                                                    acc[m % RT][m / RT], 0, 0, 0);
   };
   // keeps a quarter's reads and conversions between its products
-  auto pin = [&](auto reads, auto valu) {
-    constexpr int kM = RT * MT < 4 ? 1 : RT * MT / 4;
+  auto pin = [&](int c) {
 #pragma unroll
-    for (int i = 0; i < kM; ++i) {
+    for (int m = c * RT * MT / 4; m < (c + 1) * RT * MT / 4; ++m) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, (decltype(reads)::value + kM - 1) / kM, 0);  // LDS read
-      __builtin_amdgcn_sched_group_barrier(0x002, (decltype(valu)::value + kM - 1) / kM, 0);   // VALU
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // LDS reads
+      __builtin_amdgcn_sched_group_barrier(0x002, BITS == 16 ? 2 : 6, 0);  // VALU
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  using std::integral_constant;
 
   uint32_t as = 0, ws = 0, ss = 0;                                         // slots of stage k
   uint32_t al = R::kASlots - 1, wl = R::kWSlots - 1, sl = R::kWSlots - 1;  // slots loaded next
@@ -411,19 +415,16 @@ __device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         loads(k, 4 + 4 * s + c);
-        // LDS reads in the first half of the step, two quarters before use
-        if (c < 2) {
+        // activation fragments in the first three quarters, each at least two
+        // quarters before its use; codes one tile per quarter
 #pragma unroll
-          for (int t = c * MT / 2; t < (c + 1) * MT / 2; ++t) read_a(s + 1, t, as);
-          if (BITS == 16)
+        for (int t = 0; t < MT; ++t)
+          if (3 * t / MT == c) read_a(s + 1, t, as);
 #pragma unroll
-            for (int i = c * RT / 2; i < (c + 1) * RT / 2; ++i) read_w(s + 1, i, ws);
-        }
-        if (BITS != 16)
-#pragma unroll
-          for (int i = c * RT / 4; i < (c + 1) * RT / 4; ++i) read_w(s + 1, i, ws);
+        for (int i = 0; i < RT; ++i)
+          if (c == (BITS == 16 ? 0 : i + 1)) read_w(s + 1, i, ws);
         products(s, c);
-        pin(integral_constant<int, 4>{}, integral_constant<int, BITS == 16 ? 8 : 20>{});
+        pin(c);
       }
     }
     // every load of stage k + 1 has arrived; the slots of stage k are free
@@ -442,23 +443,16 @@ __device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       loads(k + 1, c);
-      if (c < 2) {
 #pragma unroll
-        for (int i = c * RT / 2; i < (c + 1) * RT / 2; ++i) {
-          if (BITS != 16) read_q(i, k + 1, ws, ss);
-          else read_w(0, i, ws);
-        }
+      for (int i = 0; i < RT; ++i) {
+        if (c == 0 && BITS != 16) read_q(i, k + 1, ws, ss);
+        if (c == (BITS == 16 ? 0 : i + 2)) read_w(0, i, ws);
+      }
 #pragma unroll
-        for (int t = c * MT / 2; t < (c + 1) * MT / 2; ++t) read_a(0, t, as);
-      }
-      if (BITS != 16) {  // tile 0, tiles 1 and 2, tile 3; or tile 0, tile 1
-        if (c == 1 && RT == 4) read_w(0, 0, ws);
-        if (c == 2) read_w(0, RT == 4 ? 1 : 0, ws);
-        if (c == 2 && RT == 4) read_w(0, 2, ws);
-        if (c == 3) read_w(0, RT - 1, ws);
-      }
+      for (int t = 0; t < MT; ++t)
+        if (3 * t / MT == c) read_a(0, t, as);
       products(3, c);
-      pin(integral_constant<int, BITS == 16 ? 4 : 8>{}, integral_constant<int, BITS == 16 ? 8 : 36>{});
+      pin(c);
     }
   }
   // the LDS must not be handed on with loads in flight
@@ -571,7 +565,7 @@ template <int BITS, int RT, int MT>
 __device__ __forceinline__ void up_tile(const ExpertEntry& ex, const Item& it, const int32_t* perm,
                                         const f16* x, f16* h, int d, int f, int K, lds_u8* lds) {
   const int n = min(kTileTok, it.g.count - it.tok0);
-  const int64_t row0 = (int64_t)it.tile * (32 * RT);
+  const int64_t row0 = (int64_t)it.tile * (64 * RT);
   const Sub sub = {weights_at<BITS, 0>(ex, row0, d), weights_at<BITS, 1>(ex, row0, d),
                    scales_at<BITS, 0>(ex, row0, d), scales_at<BITS, 1>(ex, row0, d),
                    f - (int)row0, f - (int)row0};
@@ -579,25 +573,23 @@ __device__ __forceinline__ void up_tile(const ExpertEntry& ex, const Item& it, c
   const int off = it.g.offset + it.tok0;
   tile_gemm<BITS, RT, MT, true>(sub, d, x, perm + off, n, K, lds, acc);
   const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t row = row0 + wave * (16 * RT);
+  if (row >= f) return;
 #pragma unroll
-  for (int c = 0; c < RT / 2; ++c) {
-    const int64_t row = row0 + (wave >> 1) * (16 * RT) + c * 32;
-    if (row >= f) continue;
+  for (int t = 0; t < MT; ++t) {
+    const int j = 32 * t + (l & 31);
+    if (j < n) {
+      f16* out = h + (int64_t)(off + j) * f + row + 4 * (l >> 5);
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int j = (wave & 1) * (32 * MT) + 32 * t + (l & 31);
-      if (j < n) {
-        f16* out = h + (int64_t)(off + j) * f + row + 4 * (l >> 5);
+      for (int q = 0; q < 2 * RT; ++q) {
+        f16x4 v;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          f16x4 v;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float a = acc[c][t][4 * q + i], b = acc[c + RT / 2][t][4 * q + i];
-            v[i] = (f16)(silu(a) * b);
-          }
-          *reinterpret_cast<f16x4*>(out + 8 * q) = v;
+        for (int i = 0; i < 4; ++i) {
+          const float a = acc[0][t][4 * q + i];
+          const float b = RT == 2 ? acc[RT - 1][t][4 * q + i] : acc[0][t][8 + 4 * (q & 1) + i];
+          v[i] = (f16)(silu(a) * b);
         }
+        *reinterpret_cast<f16x4*>(out + 8 * q) = v;
       }
     }
   }
@@ -607,9 +599,9 @@ template <int BITS, int RT, int MT>
 __device__ __forceinline__ void down_tile(const ExpertEntry& ex, const Item& it, const f16* h,
                                           float* e, int d, int f, lds_u8* lds) {
   const int n = min(kTileTok, it.g.count - it.tok0);
-  const int row0 = it.tile * (64 * RT);
+  const int row0 = it.tile * (128 * RT);
   // a tile whose second half lies past the matrix reads the first half's rows
-  const int row1 = row0 + 32 * RT < d ? row0 + 32 * RT : row0;
+  const int row1 = row0 + 64 * RT < d ? row0 + 64 * RT : row0;
   const Sub sub = {weights_at<BITS, 2>(ex, row0, f), weights_at<BITS, 2>(ex, row1, f),
                    scales_at<BITS, 2>(ex, row0, f), scales_at<BITS, 2>(ex, row1, f),
                    d - row0, d - row1};
@@ -618,18 +610,20 @@ __device__ __forceinline__ void down_tile(const ExpertEntry& ex, const Item& it,
   tile_gemm<BITS, RT, MT, false>(sub, f, h + off * f, nullptr, n, 1, lds, acc);
   const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int i = 0; i < RT; ++i) {
-    const int rw = row0 + i / (RT / 2) * (32 * RT) + (wave >> 1) * (16 * RT) + i % (RT / 2) * 32;
-    if (rw >= d) continue;
+  for (int b = 0; b < 2; ++b) {  // the wave's 16 RT rows of each sub-block
+    const int row = row0 + b * (64 * RT) + wave * (16 * RT);
+    if (row >= d) continue;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      const int j = (wave & 1) * (32 * MT) + 32 * t + (l & 31);
+      const int j = 32 * t + (l & 31);
       if (j < n) {
-        float* out = e + (off + j) * d + rw + 4 * (l >> 5);
+        float* out = e + (off + j) * d + row + 4 * (l >> 5);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<f32x4*>(out + 8 * q) =
-              f32x4{acc[i][t][4 * q], acc[i][t][4 * q + 1], acc[i][t][4 * q + 2], acc[i][t][4 * q + 3]};
+        for (int q = 0; q < 2 * RT; ++q) {
+          const f32x16& c = acc[RT == 2 ? b : 0][t];
+          const int v = RT == 2 ? 4 * q : 8 * b + 4 * (q & 1);
+          *reinterpret_cast<f32x4*>(out + 8 * q) = f32x4{c[v], c[v + 1], c[v + 2], c[v + 3]};
+        }
       }
     }
   }
@@ -638,21 +632,31 @@ __device__ __forceinline__ void down_tile(const ExpertEntry& ex, const Item& it,
 template <int BITS, int RT>
 __device__ __forceinline__ void up_item(const ExpertEntry& ex, const Item& it, const int32_t* perm,
                                         const f16* x, f16* h, int d, int f, int K, lds_u8* lds) {
-  const int n = it.g.count - it.tok0;
-  if (n > 192) up_tile<BITS, RT, 4>(ex, it, perm, x, h, d, f, K, lds);
-  else if (n > 128) up_tile<BITS, RT, 3>(ex, it, perm, x, h, d, f, K, lds);
-  else if (n > 64) up_tile<BITS, RT, 2>(ex, it, perm, x, h, d, f, K, lds);
-  else up_tile<BITS, RT, 1>(ex, it, perm, x, h, d, f, K, lds);
+  switch (min((it.g.count - it.tok0 + 31) / 32, 8)) {
+    case 1: return up_tile<BITS, RT, 1>(ex, it, perm, x, h, d, f, K, lds);
+    case 2: return up_tile<BITS, RT, 2>(ex, it, perm, x, h, d, f, K, lds);
+    case 3: return up_tile<BITS, RT, 3>(ex, it, perm, x, h, d, f, K, lds);
+    case 4: return up_tile<BITS, RT, 4>(ex, it, perm, x, h, d, f, K, lds);
+    case 5: return up_tile<BITS, RT, 5>(ex, it, perm, x, h, d, f, K, lds);
+    case 6: return up_tile<BITS, RT, 6>(ex, it, perm, x, h, d, f, K, lds);
+    case 7: return up_tile<BITS, RT, 7>(ex, it, perm, x, h, d, f, K, lds);
+    default: return up_tile<BITS, RT, 8>(ex, it, perm, x, h, d, f, K, lds);
+  }
 }
 
 template <int BITS, int RT>
 __device__ __forceinline__ void down_item(const ExpertEntry& ex, const Item& it, const f16* h,
                                           float* e, int d, int f, lds_u8* lds) {
-  const int n = it.g.count - it.tok0;
-  if (n > 192) down_tile<BITS, RT, 4>(ex, it, h, e, d, f, lds);
-  else if (n > 128) down_tile<BITS, RT, 3>(ex, it, h, e, d, f, lds);
-  else if (n > 64) down_tile<BITS, RT, 2>(ex, it, h, e, d, f, lds);
-  else down_tile<BITS, RT, 1>(ex, it, h, e, d, f, lds);
+  switch (min((it.g.count - it.tok0 + 31) / 32, 8)) {
+    case 1: return down_tile<BITS, RT, 1>(ex, it, h, e, d, f, lds);
+    case 2: return down_tile<BITS, RT, 2>(ex, it, h, e, d, f, lds);
+    case 3: return down_tile<BITS, RT, 3>(ex, it, h, e, d, f, lds);
+    case 4: return down_tile<BITS, RT, 4>(ex, it, h, e, d, f, lds);
+    case 5: return down_tile<BITS, RT, 5>(ex, it, h, e, d, f, lds);
+    case 6: return down_tile<BITS, RT, 6>(ex, it, h, e, d, f, lds);
+    case 7: return down_tile<BITS, RT, 7>(ex, it, h, e, d, f, lds);
+    default: return down_tile<BITS, RT, 8>(ex, it, h, e, d, f, lds);
+  }
 }
 
 template <int RT>
@@ -750,9 +754,9 @@ int max_blocks(int T, int K, int max_groups, int n_tiles) {
 // about 144 of them (9/16 of the 256 compute units) leave too much of the
 // chip idle.  Measured with 256 / 128 rows, half of the experts fp16 and
 // half int4: down-projection of the Mixtral-shaped layer at 512 tokens (128
-// larger blocks) 347 / 259 us, of the Phi-shaped one (256) 161 / 193 us;
-// up-projection at d 1024, f 2048, 8 experts, 512 tokens (128) 31 / 26 us,
-// 1024 tokens (192) 36 / 42 us; Mixtral-shaped at 64 tokens (896) 310 / 361.
+// larger blocks) 300 / 227 us, of the Phi-shaped one (256) 130 / 161 us;
+// up-projection at d 1024, f 2048, 8 experts, 512 tokens (128) 27 / 22 us,
+// 1024 tokens (192) 35 / 36 us; Mixtral-shaped at 512 tokens (896) 380 / 438.
 bool large_blocks(int T, int K, int E, int n_tiles) {
   const int P = T * K, g = P < E ? P : E;
   const int filled = P / kTileTok + g / 2;
@@ -768,10 +772,10 @@ hipError_t launch_prefill_up(const ExpertEntry* table, const WorkList* wl, const
   if (d % kStageK || f % 32) return hipErrorInvalidValue;
   const int n_large = (f + 127) / 128, n_small = (f + 63) / 64;
   if (large_blocks(T, K, E, n_large))
-    prefill_up_kernel<4><<<max_blocks(T, K, max_groups, n_large), kThreads, 0, s>>>(
+    prefill_up_kernel<2><<<max_blocks(T, K, max_groups, n_large), kThreads, 0, s>>>(
         table, wl, perm, x, h, d, f, K, n_large);
   else
-    prefill_up_kernel<2><<<max_blocks(T, K, max_groups, n_small), kThreads, 0, s>>>(
+    prefill_up_kernel<1><<<max_blocks(T, K, max_groups, n_small), kThreads, 0, s>>>(
         table, wl, perm, x, h, d, f, K, n_small);
   return hipGetLastError();
 }
@@ -782,10 +786,10 @@ hipError_t launch_prefill_down(const ExpertEntry* table, const WorkList* wl, con
   if (f % kStageK || d % 32) return hipErrorInvalidValue;
   const int n_large = (d + 255) / 256, n_small = (d + 127) / 128;
   if (large_blocks(T, K, E, n_large))
-    prefill_down_kernel<4><<<max_blocks(T, K, max_groups, n_large), kThreads, 0, s>>>(
+    prefill_down_kernel<2><<<max_blocks(T, K, max_groups, n_large), kThreads, 0, s>>>(
         table, wl, h, e, d, f, n_large);
   else
-    prefill_down_kernel<2><<<max_blocks(T, K, max_groups, n_small), kThreads, 0, s>>>(
+    prefill_down_kernel<1><<<max_blocks(T, K, max_groups, n_small), kThreads, 0, s>>>(
         table, wl, h, e, d, f, n_small);
   return hipGetLastError();
 }

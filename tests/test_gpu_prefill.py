@@ -149,14 +149,15 @@ def test_prefill_matches_decode():
 
 
 # One expert, so that its group has exactly T tokens: the edges of the token
-# tiles (64, 128, 192 and 256 tokens per block and the next one), the number
+# tiles (32 each, up to 256 per block) and of the next block, the number
 # of reduction stages from one (d 64) over fewer than the staging rings hold
 # to many, and weight rows that fill no tile.  d 1088 with 8192 tokens takes
 # the 256-row blocks in both projections, the others the 128-row ones.
 @pytest.mark.parametrize("tag", [C.TAG_FP16, C.TAG_INT8, C.TAG_INT4, C.TAG_INT2])
 @pytest.mark.parametrize("d,f,T", [(64, 64, 1), (64, 192, 64), (192, 64, 65), (320, 448, 128),
-                                   (576, 320, 129), (128, 704, 192), (448, 128, 193),
-                                   (832, 192, 256), (192, 832, 257), (320, 192, 513),
+                                   (576, 320, 129), (128, 704, 160), (448, 128, 193),
+                                   (256, 576, 32), (192, 448, 33), (704, 320, 96),
+                                   (64, 320, 224), (1024, 128, 225), (832, 192, 256), (192, 832, 257), (320, 192, 513),
                                    (1088, 704, 8192)])
 def test_prefill_tile_edges(tag, d, f, T):
     wl = _edge(f"prefill_edge_{tag}_{d}_{f}_{T}", 45, d, f, 1, 1, T, [tag])
