@@ -188,19 +188,22 @@ bool decode_on_matrix_cores(int T, int K, int E) {
   return T > kDecodeDot2MaxTokens || T * K > E;
 }
 
-// Large decode batches take the prefill kernels, whose blocks hold 64 tokens
-// or more: the matrix-core decode kernels stream an expert copy once per 16
-// tokens of its group, so they fall behind when most groups have more.
-// Measured per step, decode / prefill kernels: Mixtral-shaped 4:3:1 with 48
-// and 64 tokens (12 and 16 per expert) 492 / 428 and 686 / 428 us, its int8
-// model 595 / 625 and 740 / 628; d 2048, f 4096 96 / 99 and 122 / 99; Phi-
-// shaped with 64 tokens (8 per expert) 374 / 382.  On small layers latency
-// counts and the decode kernels' smaller blocks hold on longer: d 1024, f
-// 2048 with 16 per expert 51 / 54, d 320, f 448 with 16, 24 and 32 24 / 27,
-// 26 / 27 and 30 / 27 us.
+// Large decode batches take the prefill kernels: the matrix-core decode
+// kernels stream an expert copy once per 16 tokens of its group and hold
+// fewer bytes in flight; their smaller blocks win while few tokens share an
+// expert, and longer on small layers, where latency counts.  Measured per
+// step, decode / prefill kernels, at 4, 6, 8, 12 and 16 pairs per expert:
+//   Mixtral-shaped 4:3:1     336/368  392/380  426/378  494/376  686/386 us
+//   its int8 model           430/467  493/488  528/496  601/499  740/498
+//   Phi-shaped (4, 6, 8)     328/348  353/349  383/354
+//   d 2048, f 4096, 4:3:1     70/80    76/80    78/80    95/80   122/80
+//   d 1024, f 2048            31/40    32/41    33/40    42/41    51/41
+//   d 1024, f 4096, fp16      49/63    50/64    52/64    57/64    76/66
+//   d 320, f 448 (8, 12, 16)  20/23    21/23    23/23
 bool decode_on_prefill_kernels(int T, int K, int E, int d, int f) {
-  const int64_t P = (int64_t)T * K;
-  return P >= 28 * (int64_t)E || (P >= 14 * (int64_t)E && (int64_t)d * f >= (1 << 22));
+  const int64_t size = (int64_t)d * f;
+  const int per_expert = size >= (1 << 24) ? 8 : size >= (1 << 23) ? 10 : 16;
+  return (int64_t)T * K >= (int64_t)per_expert * E;
 }
 
 // The launch sequence of a decode step with the workspace `ws` (the layer's

@@ -282,11 +282,13 @@ def test_routers_of_larger_steps(d, E, K, T):
     _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, d)).astype(np.float16))
 
 
-@pytest.mark.parametrize("d,f,E,K,T", [(320, 448, 4, 2, 55), (320, 448, 4, 2, 56),
-                                       (2048, 2048, 2, 1, 27), (2048, 2048, 2, 1, 28)])
+@pytest.mark.parametrize("d,f,E,K,T", [(320, 448, 4, 2, 31), (320, 448, 4, 2, 32),
+                                       (2048, 4096, 2, 1, 19), (2048, 4096, 2, 1, 20),
+                                       (4096, 4096, 2, 1, 15), (4096, 4096, 2, 1, 16)])
 def test_large_decode_batches(d, f, E, K, T):
     """Either side of the step sizes from which decode takes the prefill
-    kernels (28 pairs per expert, 14 from d_model * d_ff = 2^22 on)."""
+    kernels (16 pairs per expert, 10 from d_model * d_ff = 2^23 on, 8 from
+    2^24 on)."""
     wl = _edge(f"edge_batch_{d}_{f}_{T}", 40, d, f, E, K, T,
                [C.TAG_MISS_INT4, C.TAG_INT2, C.TAG_INT8, C.TAG_MISS_INT2][:E], t1=0.4, t2=0.9)
     rng = np.random.default_rng(400 + T)
