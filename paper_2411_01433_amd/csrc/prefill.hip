@@ -65,11 +65,11 @@
 // Measured (one layer, up / down-projection, us; before: 16x16x32 products,
 // 16 or 32 weight rows per wave, 160 tokens per pass, weights in register
 // rings, activations through LDS):
-//   Mixtral shape, 4:3:1 fp16:int4:int2, 8192 tokens 5863 / 3407 -> 3396 /
-//   1795 (1.13 and 1.07 PFLOP/s; a large fp16 library GEMM reaches 1.48),
-//   512 tokens 455 / 292 -> 380 / 226; half fp16 half int4, 64 tokens 369 /
-//   184 -> 240 / 119 (5.0 TB/s); Phi shape, 1337 tokens 752 / 391 -> 432 /
-//   193; d 320, f 448, 6 experts, 1337 tokens 55 / 42 -> 14 / 16.
+//   Mixtral shape, 4:3:1 fp16:int4:int2, 8192 tokens 5863 / 3407 -> 3189 /
+//   1671 (1.21 and 1.15 PFLOP/s; a large fp16 library GEMM reaches 1.34 -
+//   1.48), 512 tokens 455 / 292 -> 370 / 217; half fp16 half int4, 64 tokens
+//   369 / 184 -> 260 / 130 (4.6 TB/s); Phi shape, 1337 tokens 752 / 391 ->
+//   407 / 179; d 320, f 448, 6 experts, 1337 tokens 55 / 42 -> 13 / 14.
 // On the way, at 8192 tokens and fp16 only (up): 8 waves of 64 rows x 128
 // tokens 3.85 ms; 4 waves 3.70; fragment reads two quarters early and the
 // short SwiGLU 3.60; remainders last 3.55; three activation stages instead
