@@ -21,7 +21,6 @@ constexpr int kRouteSmallTokens = 8;  // tokens a step's single router block tak
 static_assert(kMaxExperts <= kRouteThreads, "one thread per expert stages the table");
 constexpr int kRouteWaves = kRouteThreads / 64;
 constexpr int kRowChunks = 8;     // 512-column chunks of a row held in registers at once
-constexpr int kMaxTokPerBlock = 16;
 
 // fp16-pair dot product with fp32 accumulation.  The operands are taken
 // as scalars on purpose: clang's __builtin_bit_cast applied directly to a
@@ -503,12 +502,18 @@ __global__ __launch_bounds__(kRouteThreads) void worklist_kernel(
 template <bool FIRST>
 hipError_t launch_route_tokens(const RouteParams& p, RouteOut o, WorkList* wl, int32_t* perm,
                                int32_t* pos, hipStream_t s) {
-  // one token per block up to two blocks per compute unit
+  // One token per block up to two blocks per compute unit; 4 up to 2048
+  // tokens, where blocks of 16 leave half of the units or more without one
+  // (whole call at d 4096, f 64, blocks of 16 / 4: 16 experts, 513 tokens 68.3
+  // / 56.9 us, 1337 tokens 92.4 / 86.2, 2000 tokens 109.7 / 103.8; 24 experts,
+  // 1337 tokens 122.3 / 99.0); then 16, as blocks of 8 were slower at 2500 to
+  // 4096 tokens (16 experts 153.4 us, 155.7 by 8).
   if (p.T <= 512) {
     route_tokens_kernel<FIRST, 1><<<p.T, kRouteThreads, 0, s>>>(p, o);
+  } else if (p.T <= 2048) {
+    route_tokens_kernel<FIRST, 4><<<(p.T + 3) / 4, kRouteThreads, 0, s>>>(p, o);
   } else {
-    route_tokens_kernel<FIRST, kMaxTokPerBlock>
-        <<<(p.T + kMaxTokPerBlock - 1) / kMaxTokPerBlock, kRouteThreads, 0, s>>>(p, o);
+    route_tokens_kernel<FIRST, 16><<<(p.T + 15) / 16, kRouteThreads, 0, s>>>(p, o);
   }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;

@@ -175,3 +175,15 @@ def test_prefill_many_groups(E, K, T):
                t1=0.3, t2=0.9)
     x = np.random.default_rng(16).standard_normal((T, 128)).astype(np.float16)
     _check(wl, wl.fixed_tags, x, sample=np.unique(np.linspace(0, T - 1, 500).astype(int)))
+
+
+@pytest.mark.parametrize("T", [512, 513, 2047, 2048, 2049])
+@pytest.mark.parametrize("E,K", [(6, 3), (17, 2)])
+def test_prefill_router_block_sizes(E, K, T):
+    """Either side of the step sizes from which the router's blocks take 4 and
+    16 tokens, with gate rows in registers (E <= 16) and from L2."""
+    wl = _edge(f"prefill_router_{E}_{T}", 47, 128, 64, E, K, T,
+               [(C.TAG_FP16, C.TAG_MISS_INT4, C.TAG_MISS_INT2)[e % 3] for e in range(E)],
+               t1=0.3, t2=0.8)
+    x = np.random.default_rng(17).standard_normal((T, 128)).astype(np.float16)
+    _check(wl, wl.fixed_tags, x, sample=np.unique(np.linspace(0, T - 1, 400).astype(int)))
