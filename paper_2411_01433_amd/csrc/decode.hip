@@ -26,9 +26,9 @@
 // row tile, so every selected expert copy is streamed from HBM once per step
 // whatever the number of tokens routed to it.  Down-projection blocks each
 // take a row tile of d_model and loop over all work groups, accumulating
-// w[p] * e into the token's output row in LDS in work-list order (per wave
-// where a wave takes groups alone, then the waves in order), so the combine
-// needs no extra pass and the sum order is fixed (deterministic).
+// w[p] * e into the token's output row in LDS in work-list order, so the
+// combine needs no extra pass and the sum order is fixed (deterministic, and
+// the same for a token whatever step it is in).
 #include "moe_internal.h"
 
 namespace moe {
@@ -45,7 +45,10 @@ constexpr int kWaves = kThreads / 64;
 // with 4-row down tiles: 109 us).
 template <int NTMAX> struct UpRows { static constexpr int value = NTMAX <= 2 ? 2 : 4; };
 template <int NTMAX> struct DownRows { static constexpr int value = NTMAX <= 2 ? 4 : 8; };
-constexpr int kOwnGroupMaxF = 8192;  // longest rows whose groups a wave takes alone
+constexpr int kOwnGroupMaxF = 2048;  // longest rows whose groups a wave takes alone
+// most pairs of a step of these kernels: two tokens, or as many as experts
+constexpr int kMaxDot2Pairs = 64;
+static_assert(2 * kMaxTopK <= kMaxDot2Pairs && kMaxExperts <= kMaxDot2Pairs && kMaxDot2Pairs <= kThreads, "pairs");
 
 // Scalar-argument casts on purpose: clang's __builtin_bit_cast applied
 // directly to a vector component expression (v.y) reads component 0.
@@ -235,20 +238,19 @@ template <> struct Piece<2> {
   }
 };
 
-// Partial dot products of this wave's chunks (every STRIDE-th one: kWaves
-// where the waves split the reduction, 1 where a wave takes all of it) for
-// ROWS rows of NM matrices (matrix ids mats) against NT activation rows
-// act_rows[t] (length ld).
-template <int BITS, int NT, int NM, int ROWS, int STRIDE = kWaves>
+// Partial dot products of chunks first, first + kWaves, ... (a wave's own
+// number where the waves split the reduction) for ROWS rows of NM matrices
+// (matrix ids mats) against NT activation rows act_rows[t] (length ld).
+template <int BITS, int NT, int NM, int ROWS>
 __device__ inline void tile_dots(const ExpertEntry& ex, const int (&mats)[NM],
                                  int64_t row0, int64_t ld,
                                  const f16* const (&act_rows)[NT],
-                                 float (&acc)[NM][ROWS][NT]) {
+                                 float (&acc)[NM][ROWS][NT], int first) {
   constexpr int kEpl = Fmt<BITS>::kEpl;
   constexpr int kChunk = 64 * kEpl;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   const int n_chunks = (int)((ld + kChunk - 1) / kChunk);
-  for (int c = STRIDE == 1 ? 0 : wave; c < n_chunks; c += STRIDE) {
+  for (int c = first; c < n_chunks; c += kWaves) {
     const int64_t col = (int64_t)c * kChunk + lane * kEpl;
     if (col >= ld) continue;  // ragged last chunk (ld is a multiple of 64)
     uint32_t a[NT][kEpl / 2];
@@ -369,7 +371,7 @@ __device__ void up_tile(const ExpertEntry& ex, const int32_t* pairs, int n,
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[m][i][t] = 0.0f;
   const int mats[2] = {0, 1};
-  tile_dots<BITS, NT, 2, ROWS>(ex, mats, row0, d, rows, acc);
+  tile_dots<BITS, NT, 2, ROWS>(ex, mats, row0, d, rows, acc, threadIdx.x >> 6);
   block_reduce<2, NT, ROWS>(acc, red);
   const float* fin = red + kWaves * 2 * ROWS * NT;
   for (int v = threadIdx.x; v < ROWS * NT; v += kThreads) {
@@ -433,7 +435,7 @@ __device__ void down_tile(const ExpertEntry& ex, const int32_t* pairs, int n,
   // would lose a wave, and code groups measured slower with it (int8 W2
   // 24.9 -> 26.3 us per int8-model step)
   if constexpr (RING && BITS == 16) tile_dots_ring<BITS, NT, 1, ROWS>(ex, mats, row0, f, rows, acc);
-  else tile_dots<BITS, NT, 1, ROWS>(ex, mats, row0, f, rows, acc);
+  else tile_dots<BITS, NT, 1, ROWS>(ex, mats, row0, f, rows, acc, threadIdx.x >> 6);
   block_reduce<1, NT, ROWS>(acc, red);
   const float* fin = red + kWaves * ROWS * NT;
   for (int v = threadIdx.x; v < ROWS * NT; v += kThreads) {
@@ -461,57 +463,63 @@ __device__ void down_group(const ExpertEntry& ex, const int32_t* pairs, int coun
   }
 }
 
-// The same for one wave and one group, the whole reduction in this wave.
+// The unweighted sums of one wave and one group, the whole reduction in this
+// wave: out[j][i] for the group's pair j.  The chunks are taken in the
+// subsets that the waves take where they split the reduction, each summed
+// over the lanes, then the subsets in order, so that both ways give the
+// same bits and a token's result does not depend on the step it is in.
 template <int BITS, int NT, int ROWS>
 __device__ void down_tile_wave(const ExpertEntry& ex, const int32_t* pairs, int n,
-                               const f16* h, const float* gate_w, int f, int K,
-                               int64_t row0, float* yacc) {
+                               const f16* h, int f, int64_t row0, float* out) {
   const f16* rows[NT];
-  float gw[NT];
-  int tok[NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int p = pairs[t < n ? t : 0];
-    rows[t] = h + (int64_t)p * f;
-    gw[t] = gate_w[p];
-    tok[t] = p / K;
-  }
-  float acc[1][ROWS][NT];
-#pragma unroll
-  for (int i = 0; i < ROWS; ++i)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[0][i][t] = 0.0f;
+  for (int t = 0; t < NT; ++t) rows[t] = h + (int64_t)pairs[t < n ? t : 0] * f;
   const int mats[1] = {2};
-  tile_dots<BITS, NT, 1, ROWS, 1>(ex, mats, row0, f, rows, acc);
+  constexpr int kChunk = 64 * Fmt<BITS>::kEpl;
+  const int subsets = min(kWaves, (f + kChunk - 1) / kChunk);
+  float sum = 0.0f;  // lane l: row l % ROWS of pair l / ROWS % NT
+#pragma unroll 1
+  for (int w = 0; w < subsets; ++w) {
+    float acc[1][ROWS][NT], v[ROWS * NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
+    for (int i = 0; i < ROWS; ++i)
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i) {
-      const float s = wave_sum_dpp(acc[0][i][t]);
-      if ((threadIdx.x & 63) == 0 && t < n) yacc[tok[t] * ROWS + i] += gw[t] * s;
-    }
+      for (int t = 0; t < NT; ++t) acc[0][i][t] = 0.0f;
+    tile_dots<BITS, NT, 1, ROWS>(ex, mats, row0, f, rows, acc, w);
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) v[t * ROWS + i] = acc[0][i][t];
+    sum += wave_sums_dpp<ROWS * NT>(v);
+  }
+  const int lane = threadIdx.x & 63;
+  if (lane < n * ROWS) out[lane] = sum;
 }
 
 template <int BITS, int ROWS>
 __device__ void down_group_wave(const ExpertEntry& ex, const int32_t* pairs, int count,
-                                const f16* h, const float* gate_w, int f, int K,
-                                int64_t row0, float* yacc) {
+                                const f16* h, int f, int64_t row0, float* out) {
   for (int j0 = 0; j0 < count; j0 += 2) {
     const int n = min(2, count - j0);
-    if (n == 1) down_tile_wave<BITS, 1, ROWS>(ex, pairs + j0, n, h, gate_w, f, K, row0, yacc);
-    else down_tile_wave<BITS, 2, ROWS>(ex, pairs + j0, n, h, gate_w, f, K, row0, yacc);
+    if (n == 1) down_tile_wave<BITS, 1, ROWS>(ex, pairs + j0, n, h, f, row0, out + j0 * ROWS);
+    else down_tile_wave<BITS, 2, ROWS>(ex, pairs + j0, n, h, f, row0, out + j0 * ROWS);
   }
 }
 
 // y[t, rows] (or h_res[t, rows] += ...) for one row tile, all work groups.
 // The waves split each group's reduction, or, with at least as many groups as
-// waves and rows short enough (f <= 8192), every wave takes groups of its
+// waves and rows short enough (f <= 2048), every wave takes groups of its
 // own: a split group costs the block two barriers and a chain of loads
 // (group, expert, pairs, activations) that nothing overlaps, which on small
-// layers is all there is.  Per step, split / own groups: d 256, f 512, 4
-// tokens 20.5 / 15.5 us, d 1024, f 2048, 4 tokens 33.4 / 29.0; Phi-shaped
-// down-projection, 4 tokens (f 6400) 47.6 / 44.7; Mixtral-shaped (f 14336)
-// 79 / 84 us, its groups' widths differing too much to balance over a block.
+// layers is all there is.  On longer rows the subsets' sums, during which
+// the wave loads nothing, and groups of unequal size in one block eat that
+// up.  Per step, split / own groups, us (fp16 copies, or 4:3:1
+// fp16:int4:int2):
+//   d 256, f 512, 4 tokens 23.2 / 16.6; d 1024, f 2048, 4 tokens 36.3 / 30.2,
+//   8 skewed tokens fp16 56.6 / 56.1; d 4096, f 2048, 3 tokens 34.4 / 31.9
+//   d 2048, f 4096, 4 tokens 69.1 / 63.0, but d 1024, f 4096, 8 skewed tokens
+//   85.2 / 88.0, d 4096, f 4096, 4 tokens fp16 112 / 118; Phi-shaped (f 6400),
+//   4 tokens 136 / 131, 3 tokens 70.5 / 71.4; f 8192, 4 tokens fp16 209 / 227
 template <int NTMAX>
 __global__ __launch_bounds__(kThreads) void decode_down_kernel(
     const ExpertEntry* __restrict__ table, const WorkList* __restrict__ wl,
@@ -520,14 +528,16 @@ __global__ __launch_bounds__(kThreads) void decode_down_kernel(
     int T, int d, int f, int K) {
   constexpr int R = DownRows<NTMAX>::value;
   __shared__ float red[(kWaves + 1) * R * NTMAX];
-  __shared__ float yacc[kWaves * kDecodeDot2MaxTokens * R];
+  __shared__ float yacc[kDecodeDot2MaxTokens * R];
+  // own groups: every pair's sums, gate value and token, in work-list order
+  __shared__ float psum[kMaxDot2Pairs * R], pw[kMaxDot2Pairs];
+  __shared__ int ptok[kMaxDot2Pairs];
   const int64_t row0 = (int64_t)blockIdx.x * R;
   const int n_groups = wl->n_groups;
   const bool split = NTMAX == 1 || n_groups < kWaves || f > kOwnGroupMaxF;
-  const int parts = split ? 1 : kWaves;  // partial sums of y in LDS
-  for (int v = threadIdx.x; v < parts * T * R; v += kThreads) yacc[v] = 0.0f;
-  __syncthreads();
   if (split) {
+    for (int v = threadIdx.x; v < T * R; v += kThreads) yacc[v] = 0.0f;
+    __syncthreads();
     for (int gi = 0; gi < n_groups; ++gi) {
       const Group g = wl->groups[gi];
       const ExpertEntry ex = table[g.expert];
@@ -538,26 +548,37 @@ __global__ __launch_bounds__(kThreads) void decode_down_kernel(
       else down_group<2, NTMAX>(ex, pairs, g.count, h, gate_w, f, K, row0, red, yacc);
     }
   } else if constexpr (NTMAX > 1) {
+    const int n_pairs = wl->groups[n_groups - 1].offset + wl->groups[n_groups - 1].count;
+    if ((int)threadIdx.x < n_pairs) {
+      const int p = perm[threadIdx.x];
+      pw[threadIdx.x] = gate_w[p];
+      ptok[threadIdx.x] = p / K;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float* mine = yacc + wave * T * R;
     for (int gi = wave; gi < n_groups; gi += kWaves) {
       const Group g = wl->groups[gi];
       const ExpertEntry ex = table[g.expert];
       const int32_t* pairs = perm + g.offset;
-      if (g.bits == 16) down_group_wave<16, R>(ex, pairs, g.count, h, gate_w, f, K, row0, mine);
-      else if (g.bits == 8) down_group_wave<8, R>(ex, pairs, g.count, h, gate_w, f, K, row0, mine);
-      else if (g.bits == 4) down_group_wave<4, R>(ex, pairs, g.count, h, gate_w, f, K, row0, mine);
-      else down_group_wave<2, R>(ex, pairs, g.count, h, gate_w, f, K, row0, mine);
+      float* out = psum + g.offset * R;
+      if (g.bits == 16) down_group_wave<16, R>(ex, pairs, g.count, h, f, row0, out);
+      else if (g.bits == 8) down_group_wave<8, R>(ex, pairs, g.count, h, f, row0, out);
+      else if (g.bits == 4) down_group_wave<4, R>(ex, pairs, g.count, h, f, row0, out);
+      else down_group_wave<2, R>(ex, pairs, g.count, h, f, row0, out);
     }
     __syncthreads();
+    for (int v = threadIdx.x; v < T * R; v += kThreads) {
+      const int t = v / R, i = v - t * R;
+      float s = 0.0f;
+      for (int j = 0; j < n_pairs; ++j)
+        if (ptok[j] == t) s += pw[j] * psum[j * R + i];
+      yacc[v] = s;
+    }
   }
   for (int v = threadIdx.x; v < T * R; v += kThreads) {
     const int t = v / R, i = v - t * R;
     const int64_t o = (int64_t)t * d + row0 + i;
-    float s = yacc[v];
-    for (int w = 1; w < parts; ++w) s += yacc[w * T * R + v];
-    if (h_res) h_res[o] += s;
-    else y[o] = s;
+    if (h_res) h_res[o] += yacc[v];
+    else y[o] = yacc[v];
   }
 }
 

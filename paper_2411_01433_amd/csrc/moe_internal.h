@@ -82,6 +82,39 @@ __device__ inline float wave_sum_dpp(float v) {
   return __builtin_bit_cast(float, (uint32_t)r32[0]) + __builtin_bit_cast(float, (uint32_t)r32[1]);
 }
 
+// wave_sum_dpp of V = 4 or 8 values at once: lane l gets the sum of v[l % V],
+// with the bits that wave_sum_dpp gives (the same pairs are added, level by
+// level).  Of two values a lane keeps one and hands its partner the other, so
+// that each of the first levels halves the values.
+template <int V>
+__device__ inline float wave_sums_dpp(const float (&v)[V]) {
+  static_assert(V == 4 || V == 8, "two or three levels halve the values");
+  const int lane = threadIdx.x & 63;
+  float a[V / 2], b[V / 4];
+#pragma unroll
+  for (int j = 0; j < V / 2; ++j) {
+    const bool hi = lane & 1;
+    a[j] = (hi ? v[2 * j + 1] : v[2 * j]) + dpp_f<0xB1>(hi ? v[2 * j] : v[2 * j + 1]);  // lane ^ 1
+  }
+#pragma unroll
+  for (int j = 0; j < V / 4; ++j) {
+    const bool hi = lane & 2;
+    b[j] = (hi ? a[2 * j + 1] : a[2 * j]) + dpp_f<0x4E>(hi ? a[2 * j] : a[2 * j + 1]);  // lane ^ 2
+  }
+  const bool hi = V == 8 && (lane & 4);
+  const int give = __builtin_bit_cast(int, V == 4 || hi ? b[0] : b[V / 4 - 1]);
+  int got = __builtin_amdgcn_update_dpp(give, give, 0x104, 0xF, 0x5, false);  // quads 0, 2: lane + 4
+  got = __builtin_amdgcn_update_dpp(got, give, 0x114, 0xF, 0xA, false);       // quads 1, 3: lane - 4
+  float s = (hi ? b[V / 4 - 1] : b[0]) + __builtin_bit_cast(float, got);      // lane ^ 4
+  s += dpp_f<0x128>(s);                                                       // row_ror:8, lane ^ 8
+  const uint32_t u = __builtin_bit_cast(uint32_t, s);
+  const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  s = __builtin_bit_cast(float, (uint32_t)r16[0]) + __builtin_bit_cast(float, (uint32_t)r16[1]);
+  const uint32_t w = __builtin_bit_cast(uint32_t, s);
+  const auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __builtin_bit_cast(float, (uint32_t)r32[0]) + __builtin_bit_cast(float, (uint32_t)r32[1]);
+}
+
 // Max of the keys of a wave's lanes, in every lane (as wave_sum_dpp).
 template <int CTRL>
 __device__ inline uint32_t dpp_max(uint32_t v) {

@@ -296,7 +296,7 @@ def test_large_decode_batches(d, f, E, K, T):
     _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, d)).astype(np.float16), residual=True)
 
 
-@pytest.mark.parametrize("f", [64, 8192, 8256])
+@pytest.mark.parametrize("f", [64, 2048, 2112, 8192, 8256])
 @pytest.mark.parametrize("T", [2, 4])
 def test_dot2_down_projection_group_split(f, T):
     """Either side of the row length from which the down-projection's waves
@@ -305,6 +305,35 @@ def test_dot2_down_projection_group_split(f, T):
                [C.TAG_FP16, C.TAG_INT4, C.TAG_INT2, C.TAG_INT8] * 4)
     rng = np.random.default_rng(500 + T)
     _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, 64)).astype(np.float16), residual=True)
+
+
+@pytest.mark.parametrize("f", [64, 448, 2048, 2112, 8256])
+@pytest.mark.parametrize("E,K,T", [(8, 4, 2), (16, 4, 4), (16, 2, 8), (64, 8, 8)])
+def test_dot2_steps_equal_single_token_steps(E, K, T, f):
+    """A token's result does not depend on the step it is in: the sums of the
+    dot2 kernels run in the same order whether the waves split a group or
+    take groups of their own, so a step equals its tokens' single steps bit
+    for bit."""
+    wl = _edge(f"edge_singles_{E}_{K}_{T}_{f}", 42, 192, f, E, K, T,
+               [(C.TAG_FP16, C.TAG_INT8, C.TAG_INT4, C.TAG_INT2, C.TAG_MISS_INT4)[e % 5]
+                for e in range(E)], t1=0.4, t2=0.9)
+    weights = S.device_layer_weights(wl, 0)
+    L = S.make_layer(wl, wl.fixed_tags, weights, max_tokens=T)
+    rng = np.random.default_rng(600 + T + f)
+    x = torch.from_numpy(rng.standard_normal((T, 192)).astype(np.float16)).cuda()
+    h0 = torch.from_numpy(rng.standard_normal((T, 192)).astype(np.float32)).cuda()
+    y, y1 = torch.empty_like(h0), torch.empty_like(h0)
+    h, h1 = h0.clone(), h0.clone()
+    xn, xn1 = torch.empty_like(x), torch.empty_like(x)
+    L.decode_step(x, y)
+    L.decode_step_residual(x, h, xn)
+    for t in range(T):
+        L.decode_step(x[t:t + 1], y1[t:t + 1])
+        L.decode_step_residual(x[t:t + 1], h1[t:t + 1], xn1[t:t + 1])
+    torch.cuda.synchronize()
+    for a, b in ((y, y1), (h, h1), (xn, xn1)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    L.destroy()
 
 
 def test_reduction_chunks():
