@@ -36,6 +36,23 @@ __device__ inline float dot2(uint32_t a, uint32_t b, float acc) {
                                 __builtin_bit_cast(f16x2, b), acc, false);
 }
 
+// Sum over the lanes of a wave in registers, from the halves inwards (lane ^ 32,
+// 16, 8, 4, 2, 1): the order decides between experts whose logits differ in
+// their last bits, so it is part of what a caller sees.
+__device__ inline float wave_sum_inwards(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto r32 = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  v = __builtin_bit_cast(float, (uint32_t)r32[0]) + __builtin_bit_cast(float, (uint32_t)r32[1]);
+  const uint32_t w = __builtin_bit_cast(uint32_t, v);
+  const auto r16 = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  v = __builtin_bit_cast(float, (uint32_t)r16[0]) + __builtin_bit_cast(float, (uint32_t)r16[1]);
+  v += dpp_f<0x128>(v);  // row_ror:8
+  v += dpp_f<0x124>(v);  // row_ror:4 (lanes l and l ^ 8 hold the same by now)
+  v += dpp_f<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_f<0xB1>(v);   // quad_perm [1,0,3,2]
+  return v;
+}
+
 template <int TB, int KB>
 __global__ __launch_bounds__(kPredThreads) void predict_kernel(PredictParams q) {
   const int lane = threadIdx.x & 63;
@@ -76,7 +93,7 @@ __global__ __launch_bounds__(kPredThreads) void predict_kernel(PredictParams q) 
     }
 #pragma unroll
     for (int i = 0; i < TB; ++i) {
-      const float v = wave_sum_dpp(acc[i]);
+      const float v = wave_sum_inwards(acc[i]);
       if (lane == 0 && i < nt) q.logits[(int64_t)(tb0 + i) * R + r] = v;
     }
   }

@@ -142,6 +142,32 @@ def test_predictor_ties_and_rounds(T, p, E, K):
             np.testing.assert_array_equal(idx[t, j], want)
 
 
+@pytest.mark.parametrize("T,p", [(1, 2), (2, 1), (3, 2), (4, 5)])
+def test_predictor_sum_order(T, p):
+    """Every expert's logit is a sum of the same 64 numbers, one per lane, in
+    another order: the order of the wave's sum alone decides which is the
+    largest in fp32 (halves first, then inwards), and so the prediction."""
+    E, K = 64, 8
+    rng = np.random.default_rng(50 + T)
+    x = np.zeros((T, 512), dtype=np.float16)
+    x[:, ::8] = 1
+    gates, want = [], np.zeros((T, p, K), dtype=np.int64)
+    for j in range(p):
+        v = (rng.choice([-1, 1], 64) * 2.0 ** rng.uniform(-12, 14, 64)).astype(np.float16)
+        g = np.zeros((E, 512), dtype=np.float16)
+        for e in range(E):
+            g[e, ::8] = rng.permutation(v)
+        gates.append(g)
+        s = g[:, ::8].astype(np.float32)
+        while s.shape[1] > 1:
+            h = s.shape[1] // 2
+            s = s[:, :h] + s[:, h:]
+        assert len(np.unique(s)) > 2
+        want[:, j] = np.lexsort((np.arange(E), -s[:, 0].astype(np.float64)))[:K]
+    idx = _run(512, E, K, x, gates, _masks(rng, E, p))[0]
+    np.testing.assert_array_equal(idx, want)
+
+
 def test_predictor_prefill_sized():
     """512 tokens (the prefill batch), p = 2."""
     wl = C.MIXTRAL_PREFILL
