@@ -459,13 +459,16 @@ __device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// a / (1 + e^-a) on the exponential and reciprocal units (1 ulp each): the
-// result is rounded to fp16 next, and the full-range expf and division took
-// a tenth of the up-projection's time.  e^-a overflows to infinity for
-// a < -88 and the quotient then is -0, as in the exact form.
-__device__ inline float silu(float a) {
-  return a * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * a));
-}
+// The SwiGLU's gate, as in the decode kernels: 4e-8 rms and 1.8e-7 at most
+// from 64 bits.  On the exponential and reciprocal units alone the rounding of
+// the exponent's product adds |a| 2^-24: 1.7e-7 rms and 1.8e-6 at most for
+// a ~ N(0, 8^2).  That is not good enough, although it takes 3 % less time
+// (Mixtral shape, 8192 tokens 5.16 / 5.35 ms per layer, 512 tokens 540 / 557
+// us; d 320, f 448, 200 tokens 28.7 / 30.1 us); with expf and the quotient by a
+// corrected reciprocal, which is as exact, 5.22 ms, 554 and 30.1 us, but
+// infinities and quotients below 2^-126 need a select each, which takes the
+// rest.
+__device__ inline float silu(float a) { return a / (1.0f + expf(-a)); }
 
 // Work item of a block: a group's token tile and a row tile.  Items are
 // listed in two runs: first the tiles of all groups that take the largest

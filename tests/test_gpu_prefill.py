@@ -187,3 +187,38 @@ def test_prefill_router_block_sizes(E, K, T):
                t1=0.3, t2=0.8)
     x = np.random.default_rng(17).standard_normal((T, 128)).astype(np.float16)
     _check(wl, wl.fixed_tags, x, sample=np.unique(np.linspace(0, T - 1, 400).astype(int)))
+
+
+@pytest.mark.parametrize("T,call", [(64, "prefill"), (2048, "prefill"), (64, "decode_step")])
+def test_swiglu_is_exact_to_fp32(T, call):
+    """One expert with diagonal weights: a[r] = x[r] w[r], b[r] = 2^k[r] x[r]
+    and y = h, so that every SwiGLU value shows.  Gates of -8 to -25, where
+    e^-a magnifies an error of its exponent the most.  In fp32 the exponential
+    is good to 1.5 ulp (3 x 2^-24 of its value), and the sum, the quotient and
+    the product are rounded once each (2^-24): at most 6 x 2^-24 from 64
+    bits.  So h is the fp16 number next to the exact value, unless that lies
+    within that distance of the middle between two of them."""
+    import paper_2411_01433_amd as P
+    d = 512
+    rng = np.random.default_rng(70 + T)
+    w = rng.uniform(1, 2, d).astype(np.float16)
+    a = -rng.uniform(8, 25, (T, d))
+    a[:, 1::2] = np.maximum(a[:, 1::2], -18)
+    x = (a / w).astype(np.float16)
+    k = np.where(np.arange(d) % 2 == 0, 15, 10)                # h is a normal fp16 number
+    diag = lambda v: torch.diag(torch.from_numpy(v.astype(np.float16)).cuda()).contiguous()
+    wg = torch.ones((1, d), dtype=torch.float16, device="cuda")
+    w1, w3, w2 = diag(w), diag(2.0 ** k), diag(np.ones(d))
+    L = P.MoeLayer(d, d, 1, 1, T, wg, [w1], [w3], [w2])
+    y = torch.empty((T, d), dtype=torch.float32, device="cuda")
+    getattr(L, call)(torch.from_numpy(x).cuda(), y)
+    torch.cuda.synchronize()
+    L.destroy()
+    a = x.astype(np.float64) * w.astype(np.float64)
+    exact = a / (1.0 + np.exp(-a)) * (x.astype(np.float64) * 2.0 ** k)
+    ulp = 2.0 ** (np.floor(np.log2(exact)) - 10)
+    assert exact.min() > 2.0 ** -14 and exact.max() < 65504
+    off = np.abs(y.cpu().numpy() - exact) - ulp / 2              # beyond the nearest fp16 number
+    bad = off > 6 * 2.0 ** -24 * exact
+    print(f"{bad.sum()} of {bad.size} values further off; the worst by {(off / exact).max():.2e}")
+    assert not bad.any()
