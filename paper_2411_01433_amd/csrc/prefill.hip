@@ -544,9 +544,9 @@ __device__ inline bool take_item(const WorkList* wl, int n_tiles, Item& it) {
   const int tt = odd ? o1 : o0;  // the group's token tiles in this run
   const int sup = in / (kSuper * n_tiles), left = in - sup * (kSuper * n_tiles);
   const int width = min(kSuper, tt - sup * kSuper);
-  it.tile = left / width;
+  it.tile = __builtin_amdgcn_readfirstlane(left / width);
   const int t = sup * kSuper + left - it.tile * width;
-  it.tok0 = (small ? it.g.count / kTileTok : t) * kTileTok;
+  it.tok0 = __builtin_amdgcn_readfirstlane((small ? it.g.count / kTileTok : t) * kTileTok);
   return true;
 }
 static_assert(sizeof(Group) == 16 && offsetof(WorkList, groups) % 16 == 0 && kMaxKeys == 128,

@@ -34,6 +34,17 @@ def test_library_exports_every_declared_symbol():
         assert getattr(L, name) is not None
 
 
+def test_no_kernel_needs_scratch_memory():
+    """Registers spilled to memory would have the runtime allocate it for the
+    queue (moe_decode_step_noalloc must not allocate), and inside a stage loop
+    their reloads would drain the rings of loads in flight.  Read from the
+    kernels' metadata in the library built here."""
+    blob = open(B.LIB_PATH, "rb").read()
+    found = re.findall(rb"\.private_segment_fixed_size(.).{1,200}?\.symbol..(_Z\w+)\.kd", blob, re.S)
+    assert len(found) == blob.count(b".private_segment_fixed_size") and len(found) > 20
+    assert [name.decode() for size, name in found if size != b"\0"] == []
+
+
 def test_desc_layout_matches_header():
     # 6 int32 + 3 float + 1 uint32, no padding
     assert ctypes.sizeof(B.LayerDesc) == 40
