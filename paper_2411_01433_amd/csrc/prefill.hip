@@ -127,16 +127,15 @@ template <int BITS, int RT, int MT> struct Ring {
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 // 16 (4) bytes per lane from base + off to LDS at lds + 16 (4) * lane.
-// lds and base are wave-uniform.  m0 holds the LDS address (the compiler
-// keeps nothing in it on this target); one wait state is required between
-// its write and the load.
+// lds and base are wave-uniform.  m0 holds the LDS address; one wait state
+// is required between its write and the load.
 __device__ inline void lds_load16(uint32_t lds, const uint8_t* base, uint32_t off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds), "v"(off), "s"(base) : "memory");
+               :: "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 __device__ inline void lds_load4(uint32_t lds, const uint8_t* base, uint32_t off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
-               :: "s"(lds), "v"(off), "s"(base) : "memory");
+               :: "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 // All but the N newest loads of this wave are in LDS and every LDS read of
 // it has returned, then the block's barrier.

@@ -45,6 +45,20 @@ def test_no_kernel_needs_scratch_memory():
     assert [name.decode() for size, name in found if size != b"\0"] == []
 
 
+def test_inline_assembly_names_the_special_registers_it_writes():
+    """m0 is the LDS address of direct loads: a statement that writes it and
+    does not say so could overwrite a value that the compiler keeps there."""
+    csrc = os.path.join(ROOT, "paper_2411_01433_amd", "csrc")
+    seen = 0
+    for name in sorted(os.listdir(csrc)):
+        src = open(os.path.join(csrc, name)).read()
+        for text in re.findall(r"\basm\b[^;]*;", src):
+            if re.search(r"\bs_mov_b32 m0\b", text):
+                seen += 1
+                assert '"m0"' in text.rsplit(":", 1)[1], (name, text)
+    assert seen > 0
+
+
 def test_desc_layout_matches_header():
     # 6 int32 + 3 float + 1 uint32, no padding
     assert ctypes.sizeof(B.LayerDesc) == 40
