@@ -17,7 +17,15 @@ namespace moe {
 namespace {
 
 constexpr int kRouteThreads = 1024;
-constexpr int kRouteSmallTokens = 8;  // tokens a step's single router block takes
+// Most tokens of a step that one block routes.  With more, a block per token
+// and a second kernel for the work list: from 9 tokens on that is faster but
+// for a few tokens of few experts.  Whole steps by one block / by both, us, at
+// 9 and 16 tokens: d 256, 8 experts 18.0 / 18.9, 20.4 / 19.2; d 1024, 8
+// experts 29.3 / 28.8, 33.0 / 30.2; d 4096, 16 experts (f 6400) 228 / 218, 275
+// / 258; d 512, 64 experts 45.9 / 36.6, 60.2 / 42.7.  With the norm formed by
+// the router block (one launch instead of three): d 256 22.6 / 21.6, 27.3 /
+// 22.0; d 2048, 8 experts (f 4096) 73.0 / 69.7, 83.3 / 74.7.
+constexpr int kRouteSmallTokens = 8;
 static_assert(kMaxExperts <= kRouteThreads, "one thread per expert stages the table");
 constexpr int kRouteWaves = kRouteThreads / 64;
 constexpr int kRowChunks = 8;     // 512-column chunks of a row held in registers at once
@@ -499,22 +507,10 @@ __global__ __launch_bounds__(kRouteThreads) void worklist_kernel(
   }
 }
 
-template <bool FIRST>
+template <bool FIRST, int TPB>
 hipError_t launch_route_tokens(const RouteParams& p, RouteOut o, WorkList* wl, int32_t* perm,
                                int32_t* pos, hipStream_t s) {
-  // One token per block up to two blocks per compute unit; 4 up to 2048
-  // tokens, where blocks of 16 leave half of the units or more without one
-  // (whole call at d 4096, f 64, blocks of 16 / 4: 16 experts, 513 tokens 68.3
-  // / 56.9 us, 1337 tokens 92.4 / 86.2, 2000 tokens 109.7 / 103.8; 24 experts,
-  // 1337 tokens 122.3 / 99.0); then 16, as blocks of 8 were slower at 2500 to
-  // 4096 tokens (16 experts 153.4 us, 155.7 by 8).
-  if (p.T <= 512) {
-    route_tokens_kernel<FIRST, 1><<<p.T, kRouteThreads, 0, s>>>(p, o);
-  } else if (p.T <= 2048) {
-    route_tokens_kernel<FIRST, 4><<<(p.T + 3) / 4, kRouteThreads, 0, s>>>(p, o);
-  } else {
-    route_tokens_kernel<FIRST, 16><<<(p.T + 15) / 16, kRouteThreads, 0, s>>>(p, o);
-  }
+  route_tokens_kernel<FIRST, TPB><<<(p.T + TPB - 1) / TPB, kRouteThreads, 0, s>>>(p, o);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   worklist_kernel<<<1, kRouteThreads, 0, s>>>(p, o, wl, perm, pos);
@@ -529,14 +525,22 @@ hipError_t launch_route_decode(const RouteParams& p, RouteOut o, WorkList* wl,
                                int32_t* perm, int32_t* pos, hipStream_t s) {
   // the fused RMSNorm exists on the LDS-staged gate path only
   if (p.h_res && !route_decode_fuses_norm(p.T, p.d)) return hipErrorInvalidValue;
-  if (p.T > kRouteSmallTokens) return launch_route_tokens<false>(p, o, wl, perm, pos, s);
+  if (p.T > kRouteSmallTokens) return launch_route_tokens<false, 1>(p, o, wl, perm, pos, s);
   route_decode_kernel<<<1, kRouteThreads, 0, s>>>(p, o, wl, perm, pos);
   return hipGetLastError();
 }
 
 hipError_t launch_route_prefill(const RouteParams& p, RouteOut o, WorkList* wl,
                                 int32_t* perm, int32_t* pos, hipStream_t s) {
-  return launch_route_tokens<true>(p, o, wl, perm, pos, s);
+  // One token per block up to two blocks per compute unit; 4 up to 2048
+  // tokens, where blocks of 16 leave half of the units or more without one
+  // (whole call at d 4096, f 64, blocks of 16 / 4: 16 experts, 513 tokens 68.3
+  // / 56.9 us, 1337 tokens 92.4 / 86.2, 2000 tokens 109.7 / 103.8; 24 experts,
+  // 1337 tokens 122.3 / 99.0); then 16, as blocks of 8 were slower at 2500 to
+  // 4096 tokens (16 experts 153.4 us, 155.7 by 8).
+  if (p.T <= 512) return launch_route_tokens<true, 1>(p, o, wl, perm, pos, s);
+  if (p.T <= 2048) return launch_route_tokens<true, 4>(p, o, wl, perm, pos, s);
+  return launch_route_tokens<true, 16>(p, o, wl, perm, pos, s);
 }
 
 }  // namespace moe
