@@ -52,8 +52,7 @@ struct Group {
 
 struct WorkList {
   int32_t n_groups;
-  int32_t max_count;   // largest group (tokens of the busiest expert copy)
-  int32_t pad[2];
+  int32_t pad[3];      // the groups are read 16 bytes at a time
   Group groups[kMaxKeys];
 };
 

@@ -281,7 +281,7 @@ __device__ void worklist_wave(const RouteParams& p, const int32_t* idx, const in
     else pos[lane] = -1;
   }
   const uint64_t lower = (1ull << lane) - 1ull;
-  int off = 0, ng = 0, mx = 0;
+  int off = 0, ng = 0;
   for (int k = 0; k < 2 * p.E; ++k) {
     const uint64_t m = __ballot(key == k);
     if (m == 0) continue;
@@ -301,12 +301,8 @@ __device__ void worklist_wave(const RouteParams& p, const int32_t* idx, const in
     }
     ++ng;
     off += c;
-    mx = c > mx ? c : mx;
   }
-  if (lane == 0) {
-    wl->n_groups = ng;
-    wl->max_count = mx;
-  }
+  if (lane == 0) wl->n_groups = ng;
 }
 
 // Steps of up to kRouteSmallTokens tokens: one block routes every token and
@@ -452,7 +448,7 @@ __global__ __launch_bounds__(kRouteThreads) void worklist_kernel(
       for (int w = 0; w < kRouteWaves; ++w) cnt[h] += at[w][2 * lane + h];
     }
     const int mine = cnt[0] + cnt[1], mine_g = (cnt[0] > 0) + (cnt[1] > 0);
-    int off = mine, ng = mine_g, mx = max(cnt[0], cnt[1]);
+    int off = mine, ng = mine_g;
 #pragma unroll
     for (int s = 1; s < 64; s <<= 1) {
       const int a = __shfl_up(off, s, 64), b = __shfl_up(ng, s, 64);
@@ -460,12 +456,8 @@ __global__ __launch_bounds__(kRouteThreads) void worklist_kernel(
         off += a;
         ng += b;
       }
-      mx = max(mx, __shfl_xor(mx, s, 64));
     }
-    if (lane == 63) {
-      wl->n_groups = ng;
-      wl->max_count = mx;
-    }
+    if (lane == 63) wl->n_groups = ng;
     off -= mine;
     ng -= mine_g;
 #pragma unroll
