@@ -296,6 +296,18 @@ def test_large_decode_batches(d, f, E, K, T):
     _layer_case(wl, wl.fixed_tags, rng.standard_normal((T, d)).astype(np.float16), residual=True)
 
 
+def test_large_decode_batch_in_large_blocks():
+    """The largest decode step on the prefill kernels' 256-row blocks (16
+    experts x 9 row tiles in both projections), one token tile per group, every
+    width."""
+    wl = _edge("edge_batch_large", 43, 2112, 1088, 16, 4, 64,
+               [C.TAG_FP16, C.TAG_INT8, C.TAG_INT4, C.TAG_INT2, C.TAG_MISS_INT4, C.TAG_MISS_INT2,
+                C.TAG_MISS_INT8_INT2, C.TAG_INT8] * 2, t1=0.4, t2=0.9)
+    rng = np.random.default_rng(464)
+    _layer_case(wl, wl.fixed_tags, rng.standard_normal((64, 2112)).astype(np.float16))
+    _layer_case(wl, wl.fixed_tags, rng.standard_normal((64, 2112)).astype(np.float16), residual=True)
+
+
 @pytest.mark.parametrize("f", [64, 2048, 2112, 8192, 8256])
 @pytest.mark.parametrize("T", [2, 4])
 def test_dot2_down_projection_group_split(f, T):

@@ -166,6 +166,19 @@ def test_prefill_tile_edges(tag, d, f, T):
     _check(wl, wl.fixed_tags, x, sample=sample)
 
 
+# The same in the 256-row blocks of both projections, whose rings differ with
+# the number of token tiles in the last block: one expert with 31 full blocks
+# and a remainder of 1 to 7 tiles of 32 tokens (the 8 tiles are above).
+@pytest.mark.parametrize("tag", [C.TAG_FP16, C.TAG_INT8, C.TAG_INT4, C.TAG_INT2])
+@pytest.mark.parametrize("rest", [1, 33, 65, 97, 129, 161, 193])
+def test_prefill_large_block_remainders(tag, rest):
+    d, f, T = 1088, 704, 31 * 256 + rest
+    wl = _edge(f"prefill_rest_{tag}_{rest}", 48, d, f, 1, 1, T, [tag])
+    x = np.random.default_rng(18).standard_normal((T, d)).astype(np.float16)
+    _check(wl, wl.fixed_tags, x, sample=np.r_[np.linspace(0, T - rest - 1, 40).astype(int),
+                                              T - rest:T])
+
+
 @pytest.mark.parametrize("E,K,T", [(64, 8, 700), (64, 1, 8192), (3, 2, 4000)])
 def test_prefill_many_groups(E, K, T):
     """Work lists of up to 128 groups (both copies of every expert), of groups

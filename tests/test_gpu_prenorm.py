@@ -46,6 +46,8 @@ CASES = [
     _wl("prenorm_t16_d4096", 62, 4096, 512, 8, 2, 16, 2),
     # d_model 8192: above the router's register chunks, norm kernel first
     _wl("prenorm_d8192", 63, 8192, 256, 4, 2, 2, 2, "half"),
+    # 40 tokens, 20 pairs per expert: prefill kernels, norm kernel first
+    _wl("prenorm_t40_prefill_kernels", 66, 320, 448, 4, 2, 40, 3),
     # one token: dot2 one-token kernels
     _wl("prenorm_t1", 64, 2048, 1024, 8, 2, 1, 3),
 ]
