@@ -193,13 +193,18 @@ bool decode_on_matrix_cores(int T, int K, int E) {
 // fewer bytes in flight; their smaller blocks win while few tokens share an
 // expert, and longer on small layers, where latency counts.  Measured per
 // step, decode / prefill kernels, at 4, 6, 8, 12 and 16 pairs per expert:
-//   Mixtral-shaped 4:3:1     336/368  392/380  426/378  494/376  686/386 us
-//   its int8 model           430/467  493/488  528/496  601/499  740/498
-//   Phi-shaped (4, 6, 8)     328/348  353/349  383/354
-//   d 2048, f 4096, 4:3:1     70/80    76/80    78/80    95/80   122/80
-//   d 1024, f 2048            31/40    32/41    33/40    42/41    51/41
-//   d 1024, f 4096, fp16      49/63    50/64    52/64    57/64    76/66
-//   d 320, f 448 (8, 12, 16)  20/23    21/23    23/23
+//   Mixtral-shaped 4:3:1     373/418  389/417  425/418  501/421  713/421 us
+//   its int8 model           426/444  445/444  495/444  577/452  790/490
+//   Phi-shaped (4, 6, 8)     320/389  349/389  375/389
+//   d 2048, f 4096, 4:3:1     72/81    75/82    79/81    91/81   120/81
+//     (10 pairs 84/81)
+//   d 1024, f 2048            30/40    31/41    32/41    36/41    45/41
+//   d 1024, f 4096, fp16      47/51    51/51    51/51    56/51    72/51
+//   d 320, f 448 (8, 12, 16, 20, 24)  20/23  22/23  21/23  24/24  26/24
+//   d 256, f 512 (8, 12, 16)  20/23    20/23    25/23
+// The lines lie where most of a size class has crossed.  A Phi-shaped step of
+// 64 evenly spread tokens, the most it can have, loses 4 %; with tokens that
+// favour some experts it gains (490 -> 306 us, router included).
 bool decode_on_prefill_kernels(int T, int K, int E, int d, int f) {
   const int64_t size = (int64_t)d * f;
   const int per_expert = size >= (1 << 24) ? 8 : size >= (1 << 23) ? 10 : 16;

@@ -110,10 +110,14 @@ __global__ __launch_bounds__(kPredThreads) void predict_kernel(PredictParams q) 
   if ((int)threadIdx.x < q.p) s_need[threadIdx.x] = 0ull;
   __syncthreads();
   // One wave per (token, layer), lanes are experts, while that is at most two
-  // rounds of the block's waves (one token, four layers: the kernel 7.9 ->
-  // 6.2 us); else one thread each, which walks the logits by itself but takes
-  // all of them at once (8 tokens, 8 layers: 14.5 us per call against 29 by
-  // waves).
+  // rounds of the block's waves; else one thread each, which walks the E logits
+  // K times by itself, but all pairs at once.  The line is the one of 8
+  // experts, top-2 (the whole call, waves / threads: 4 pairs 6.2 / 7.9 us, 9
+  // pairs 9.2 / 8.3, 16 pairs 10.6 / 8.5, 64 pairs 27 / 10).  The threads' walk
+  // grows with E K, so that with more experts they are ahead later only: with
+  // 16, top-2, from 16 pairs on (9 pairs 9.2 / 10.2, 24 pairs 14.1 / 11.5), with
+  // 32, top-4, past 32 pairs (20.8 / 24.5; 64 pairs 36.7 / 29.5), with 64,
+  // top-8, past 64 (9 pairs 13.6 / 64.5, 64 pairs 57 / 86, 512 pairs 358 / 232).
   if (q.T * q.p <= 2 * (kPredThreads / 64)) {
     for (int v = threadIdx.x >> 6; v < q.T * q.p; v += kPredThreads / 64) {
       const int t = v / q.p, j = v - (v / q.p) * q.p;

@@ -25,8 +25,8 @@
 // wave owns RT tiles of 32 rows and all of the tokens, MT tiles of 32: each
 // code is dequantised by one wave, and a block computes no more than 31
 // tokens too many.  With the waves 2 x 2 over rows and tokens instead, codes
-// were dequantised twice and tokens came in steps of 64: 512 tokens 604 ->
-// 539 us per layer, 64 tokens 432 -> 371, 8192 tokens 5278 -> 5097 (all fp16:
+// were dequantised twice and tokens came in steps of 64: a Mixtral-shaped
+// layer took 11 % less time at 512 tokens, 14 % at 64, 3 % at 8192 (all fp16:
 // no change, although a step now reads 10 fragments for 16 products, not 8).
 //
 // Staging.  Both operands go to LDS by direct global-to-LDS loads of 16
@@ -34,8 +34,8 @@
 // of 64 columns, 8 rows x one full 128-byte line per load; fp16 weights the
 // same; codes as they are stored, in units of 64 bytes per row (16 rows per
 // load) = 1, 2 or 4 stages of int8, int4 or int2; group scales in units of
-// 16 bytes per row = 4 stages.  Each sits in a ring of 3 to 8 slots (see
-// Ring).  A code row whose last unit is partial reads its first chunk
+// 16 bytes per row = 4 stages.  Each sits in a ring of 3 to 8 slots, the
+// weights of the largest fp16 blocks in one of 2 (see Ring).  A code row whose last unit is partial reads its first chunk
 // instead, and scales past the row its last dword, which no product uses;
 // rows past the matrix or the group repeat the last one and are not stored.
 // Nothing outside a row is read.
@@ -62,19 +62,20 @@
 // assembly without register results (the compiler would otherwise wait for
 // all of them before every LDS read); the waits are explicit counts.
 //
-// Measured (one layer, up / down-projection, us; before: 16x16x32 products,
-// 16 or 32 weight rows per wave, 160 tokens per pass, weights in register
-// rings, activations through LDS):
-//   Mixtral shape, 4:3:1 fp16:int4:int2, 8192 tokens 5863 / 3407 -> 3189 /
-//   1671 (1.21 and 1.15 PFLOP/s; a large fp16 library GEMM reaches 1.34 -
-//   1.48), 512 tokens 455 / 292 -> 370 / 217; half fp16 half int4, 64 tokens
-//   369 / 184 -> 260 / 130 (4.6 TB/s); Phi shape, 1337 tokens 752 / 391 ->
-//   407 / 179; d 320, f 448, 6 experts, 1337 tokens 55 / 42 -> 13 / 14.
-// On the way, at 8192 tokens and fp16 only (up): 8 waves of 64 rows x 128
-// tokens 3.85 ms; 4 waves 3.70; fragment reads two quarters early and the
-// short SwiGLU 3.60; remainders last 3.55; three activation stages instead
-// of two 3.38.  Blocks in the order of copy widths, or fp16 and narrow ones
-// alternating, moved nothing (512 tokens 546 - 552 us).
+// Measured (one layer, up / down-projection, us, sustained, both sides in one
+// session; before: 16x16x32 products, 16 or 32 weight rows per wave, 160
+// tokens per pass, weights in register rings, activations through LDS):
+//   Mixtral shape, 4:3:1 fp16:int4:int2, 8192 tokens 5747 / 3448 -> 3405 /
+//   1791 (1.13 and 1.07 PFLOP/s; a large fp16 library GEMM reaches 1.34 -
+//   1.48), 512 tokens 406 / 232 -> 363 / 183; half fp16 half int4, 64 tokens
+//   336 / 173 -> 278 / 133 (4.3 and 4.5 TB/s); Phi shape, 1337 tokens 664 /
+//   354 -> 384 / 161; d 320, f 448, 6 experts, 1337 tokens 53 / 40 -> 16 / 17.
+// On the way, at 8192 tokens and fp16 only (up, with a SwiGLU on the
+// exponential and reciprocal units from the third figure on): 8 waves of 64
+// rows x 128 tokens 3.85 ms; 4 waves 3.70; fragment reads two quarters early
+// 3.60; remainders last 3.55; three activation stages instead of two 3.38.
+// Blocks in the order of copy widths, or fp16 and narrow ones alternating,
+// moved nothing at 512 tokens.
 #include <cstddef>
 
 #include "moe_internal.h"
@@ -461,12 +462,11 @@ __device__ __forceinline__ void tile_gemm(const Sub& sub, int ld, const f16* act
 // The SwiGLU's gate, as in the decode kernels: 4e-8 rms and 1.8e-7 at most
 // from 64 bits.  On the exponential and reciprocal units alone the rounding of
 // the exponent's product adds |a| 2^-24: 1.7e-7 rms and 1.8e-6 at most for
-// a ~ N(0, 8^2).  That is not good enough, although it takes 3 % less time
-// (Mixtral shape, 8192 tokens 5.16 / 5.35 ms per layer, 512 tokens 540 / 557
-// us; d 320, f 448, 200 tokens 28.7 / 30.1 us); with expf and the quotient by a
-// corrected reciprocal, which is as exact, 5.22 ms, 554 and 30.1 us, but
-// infinities and quotients below 2^-126 need a select each, which takes the
-// rest.
+// a ~ N(0, 8^2).  That loses precision, although it takes 1 to 4 % less time
+// (a call of the Mixtral shape, 8192 tokens 5.24 / 5.33 ms, 512 tokens 551 /
+// 561 us; d 320, f 448, 1337 tokens 47.5 / 49.6 us).  expf with the quotient
+// by a corrected reciprocal is as exact and gains up to 1 %, but infinities
+// and quotients below 2^-126 then need a select each, which takes that back.
 __device__ inline float silu(float a) { return a / (1.0f + expf(-a)); }
 
 // Work item of a block: a group's token tile and a row tile.  Items are
@@ -754,11 +754,12 @@ int max_blocks(int T, int K, int max_groups, int n_tiles) {
 // fewer than 256 tokens, half a tile more than its tokens fill otherwise.
 // The larger blocks read less from L2 and LDS per product, but fewer than
 // about 144 of them (9/16 of the 256 compute units) leave too much of the
-// chip idle.  Measured with 256 / 128 rows, half of the experts fp16 and
-// half int4: down-projection of the Mixtral-shaped layer at 512 tokens (128
-// larger blocks) 300 / 227 us, of the Phi-shaped one (256) 130 / 161 us;
-// up-projection at d 1024, f 2048, 8 experts, 512 tokens (128) 27 / 22 us,
-// 1024 tokens (192) 35 / 36 us; Mixtral-shaped at 512 tokens (896) 380 / 438.
+// chip idle.  Measured with 256 / 128 rows, us, half of the experts fp16 and
+// half int4: down-projection of the Mixtral-shaped layer at 64 and 512 tokens
+// (128 larger blocks) 183 / 132 and 246 / 181, of the Phi-shaped one at 512
+// (256) 129 / 141; up-projection at d 1024, f 2048, 8 experts, 512 tokens
+// (128) 28.8 / 22.9, 1024 tokens (192) 36.9 / 38.9, Mixtral-shaped at 512
+// tokens (896) 369 / 382, at 8192 (4:3:1) 3280 / 3924.
 bool large_blocks(int T, int K, int E, int n_tiles) {
   const int P = T * K, g = P < E ? P : E;
   const int filled = P / kTileTok + g / 2;
