@@ -112,8 +112,8 @@ __global__ __launch_bounds__(kPredThreads) void predict_kernel(PredictParams q) 
   // One wave per (token, layer), lanes are experts, while that is at most two
   // rounds of the block's waves; else one thread each, which walks the E logits
   // K times by itself, but all pairs at once.  The line is the one of 8
-  // experts, top-2 (the whole call, waves / threads: 4 pairs 6.2 / 7.9 us, 9
-  // pairs 9.2 / 8.3, 16 pairs 10.6 / 8.5, 64 pairs 27 / 10).  The threads' walk
+  // experts, top-2 (waves / threads: the kernel at 4 pairs 6.2 / 7.9 us, whole
+  // calls at 9 pairs 9.2 / 8.3, 16 pairs 10.6 / 8.5, 64 pairs 27 / 10).  The threads' walk
   // grows with E K, so that with more experts they are ahead later only: with
   // 16, top-2, from 16 pairs on (9 pairs 9.2 / 10.2, 24 pairs 14.1 / 11.5), with
   // 32, top-4, past 32 pairs (20.8 / 24.5; 64 pairs 36.7 / 29.5), with 64,
